@@ -116,6 +116,22 @@ def _ptr(t):
     return t.ctypes.data
 
 
+_torch = None
+_KINDS = None
+_raw_stream = None
+
+
+def _load_torch():
+    global _torch, _KINDS, _raw_stream
+    import torch
+    two = {d for d in (getattr(torch, n, None) for n in ("bfloat16", "float16", "int16", "uint16")) if d is not None}
+    _KINDS = {"i32": {torch.int32}, "b16": two, "f32": {torch.float32}}
+    # the current stream's handle without a Stream object around it, where torch has it
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    _torch = torch
+    return torch
+
+
 def _dev(t, what: str, kind: str, min_numel: int = 0, nullable: bool = False):
     """Device address of a caller tensor after checking what the C ABI will assume
     of it: a contiguous CUDA tensor whose element type matches `kind` ("i32": int32
@@ -126,17 +142,15 @@ def _dev(t, what: str, kind: str, min_numel: int = 0, nullable: bool = False):
         if nullable:
             return None
         raise ValueError(f"{what}: a device tensor is required")
-    import torch
+    torch = _torch or _load_torch()
     if not isinstance(t, torch.Tensor):
         raise ValueError(f"{what}: expected a torch tensor, got {type(t).__name__}")
     if not t.is_cuda:
         raise ValueError(f"{what}: tensor is not on a GPU")
     if not t.is_contiguous():
         raise ValueError(f"{what}: tensor is not contiguous")
-    ok = {"i32": t.dtype == torch.int32,
-          "b16": t.element_size() == 2 and t.dtype != torch.bool,
-          "f32": t.dtype == torch.float32}[kind]
-    if not ok:
+    # the types in everyday use by a table; any other 2-byte type that is not bool by its size
+    if t.dtype not in _KINDS[kind] and not (kind == "b16" and t.element_size() == 2 and t.dtype != torch.bool):
         want = {"i32": "torch.int32", "b16": "a 2-byte dtype (bf16 bits)", "f32": "torch.float32"}[kind]
         raise ValueError(f"{what}: dtype {t.dtype}, expected {want}")
     if t.numel() < min_numel:
@@ -149,16 +163,29 @@ def _pool_numel(layout) -> int:
             * int(layout.page_size) * int(layout.head_dim))
 
 
+_I32 = np.dtype(np.int32)
+
+
 def _host_i32(x):
+    # an int32 array is read where it is (within the call); anything else is converted and range-checked
+    if type(x) is np.ndarray and x.dtype == _I32 and x.flags.c_contiguous and x.ndim > 0:
+        return x
     a = np.ascontiguousarray(np.asarray(x, dtype=np.int64))
     if a.size and (a.min() < -2**31 or a.max() >= 2**31):
         raise OverflowError("value does not fit int32")
     return np.ascontiguousarray(a, dtype=np.int32)
 
 
+def _total(a) -> int:
+    """Sum of a host int32 array, in Python's integers (numpy's reduction costs more on a short one)."""
+    return sum(a.tolist()) if a.size <= 64 and a.ndim == 1 else int(a.sum(dtype=np.int64))
+
+
 def _stream(stream):
     if stream is None:
-        import torch
+        torch = _torch or _load_torch()
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     if hasattr(stream, "cuda_stream"):
         return stream.cuda_stream
@@ -236,7 +263,7 @@ def sa_kv_append(ctx, layout: Layout, layer: int, k_pool, v_pool, k_new, v_new, 
     if start.shape != new_len.shape:
         raise ValueError("start and new_len differ in length")
     B = len(new_len)
-    rows = int(new_len.astype(np.int64).sum()) * int(layout.num_kv_heads) * int(layout.head_dim)
+    rows = _total(new_len) * int(layout.num_kv_heads) * int(layout.head_dim)
     _check(load_library().sa_kv_append(
         _ctx_handle(ctx), ctypes.byref(layout), int(layer),
         _dev(k_pool, "k_pool", "b16", _pool_numel(layout)), _dev(v_pool, "v_pool", "b16", _pool_numel(layout)),
@@ -298,7 +325,7 @@ def sa_kv_assemble_append(ctx, layout: Layout, k_src, v_src, k_dst, v_dst, src_l
     ks, vs, kd, vd, src, fr, nfr, dip, dix, cap = _splice_dev(layout, B, k_src, v_src, k_dst, v_dst,
                                                               src_indptr, src_indices, fresh, dst_indptr,
                                                               dst_indices)
-    rows = int(new_len.astype(np.int64).sum()) * int(layout.num_kv_heads) * int(layout.head_dim)
+    rows = _total(new_len) * int(layout.num_kv_heads) * int(layout.head_dim)
     dst_len = np.zeros(B, dtype=np.int32)
     _check(load_library().sa_kv_assemble_append(
         _ctx_handle(ctx), ctypes.byref(layout), ks, vs, kd, vd, B, _ptr(src_len), _ptr(keep_indptr),
@@ -327,7 +354,7 @@ def sa_kv_splice_alias(ctx, layout: Layout, src_len, keep_indptr, keep_spans, re
 
 
 def _attn_dev(layout, q_len, q, o, lse):
-    T = int(q_len.astype(np.int64).sum())
+    T = _total(q_len)
     n = T * int(layout.num_q_heads) * int(layout.head_dim)
     return (_dev(q, "q", "b16", n, nullable=T == 0), _dev(o, "o", "b16", n, nullable=T == 0),
             _dev(lse, "lse", "f32", T * int(layout.num_q_heads), nullable=True), T)

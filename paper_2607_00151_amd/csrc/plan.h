@@ -221,10 +221,9 @@ inline sa_status plan_splice_append(const sa_layout* layout, int32_t batch, cons
 
 // ---------------------------------------------------------------- attention
 
-// Shape checks of an attention call and its sequence records.
-inline sa_status plan_attn_check(const sa_layout* layout, int32_t layer, int32_t batch, const int32_t* h_q_len,
-                                 const int32_t* h_kv_len, float softmax_scale, std::vector<SeqDesc>& seqs,
-                                 int64_t& total_q, std::string& err) {
+// Checks of an attention call that do not look at the lengths.
+inline sa_status check_attn_call(const sa_layout* layout, int32_t layer, int32_t batch, const int32_t* h_q_len,
+                                 const int32_t* h_kv_len, float softmax_scale, std::string& err) {
   sa_status s = check_layout(layout, err);
   if (s != SA_OK) return s;
   if (layer < 0 || layer >= layout->num_layers)
@@ -233,6 +232,15 @@ inline sa_status plan_attn_check(const sa_layout* layout, int32_t layer, int32_t
   if (!h_q_len || !h_kv_len) return plan_fail(err, SA_ERR_NULL, "h_q_len / h_kv_len is NULL");
   if (!std::isfinite(softmax_scale) || softmax_scale <= 0.f)
     return plan_fail(err, SA_ERR_SHAPE, "softmax_scale must be finite and positive");
+  return SA_OK;
+}
+
+// Shape checks of an attention call and its sequence records.
+inline sa_status plan_attn_check(const sa_layout* layout, int32_t layer, int32_t batch, const int32_t* h_q_len,
+                                 const int32_t* h_kv_len, float softmax_scale, std::vector<SeqDesc>& seqs,
+                                 int64_t& total_q, std::string& err) {
+  const sa_status s = check_attn_call(layout, layer, batch, h_q_len, h_kv_len, softmax_scale, err);
+  if (s != SA_OK) return s;
   const int G = layout->num_q_heads / layout->num_kv_heads;
   seqs.assign(batch, SeqDesc{0, 0, 0, 0});
   total_q = 0;
@@ -421,7 +429,7 @@ inline void plan_attn_items(const sa_layout* layout, const std::vector<SeqDesc>&
   // key-range parts of split items share no K/V with their neighbours and
   // keep the plain longest-first order.
   {
-    std::map<int64_t, int64_t> group_len;                       // (seq, kvh) -> longest row tile
+    std::vector<int64_t> group_len((size_t)batch * Hkv, 0);     // (seq, kvh) -> longest row tile
     auto grouped = [](const Work& w) { return !w.decode && w.it.part < 0; };
     for (const Work& w : work)
       if (grouped(w)) {

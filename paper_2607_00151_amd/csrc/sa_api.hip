@@ -60,6 +60,42 @@ struct PlanImage {
   }
 };
 
+// The host arrays a plan was made from, kept to tell whether the next call of
+// the same kind asks for the same plan again (a model runs one plan through
+// all its layers): equal values, then the device's copy is used as it is and
+// nothing is planned or compared beyond these few integers.  Bound: the host,
+// wherever the kernels take less than the call (a decode step of 4 requests,
+// kernels 23 us: 24.8 us of host work a call with planning and the binding's
+// array conversions, 13.0 without; splice, append and attention over 32
+// contexts, 140 us against 34).
+class PlanKey {
+ public:
+  // true if the arrays and scalars given since begin() equal the stored ones
+  void begin() { at_ = 0; same_ = true; }
+  void add(const int32_t* v, size_t n) {
+    if (same_ && at_ + n <= words_.size() && (n == 0 || memcmp(words_.data() + at_, v, n * sizeof(int32_t)) == 0)) {
+      at_ += n;
+      return;
+    }
+    same_ = false;
+    words_.resize(at_);
+    if (n) words_.insert(words_.end(), v, v + n);
+    at_ += n;
+  }
+  bool end() {
+    if (at_ != words_.size()) {
+      words_.resize(at_);
+      same_ = false;
+    }
+    return same_;
+  }
+
+ private:
+  std::vector<int32_t> words_;
+  size_t at_ = 0;
+  bool same_ = false;
+};
+
 enum PlanKind { kPlanAppend = 0, kPlanAssemble = 1, kPlanAttn = 2, kPlanAlias = 3, kPlanKinds = 4 };
 
 // Fixed device scratch of sa_segment_prefill_attn_noalloc: the launch's plan
@@ -109,7 +145,27 @@ struct sa_ctx {
     std::vector<uint8_t> shadow;   // what the device buffer holds
     void* stream = nullptr;        // stream that last wrote it
     bool valid = false;
+    PlanKey key;                   // the arrays of the call whose plan it holds
+    bool key_valid = false;
+    bool reusable(bool same, hipStream_t st) const { return same && key_valid && valid && stream == (void*)st; }
   } plans[kPlanKinds];
+  // what a launch needs of the plans the device holds
+  struct AppendRec {
+    size_t o_tok = 0, o_start = 0;
+    int64_t total = 0;
+  } append_rec;
+  struct SpliceRec {
+    std::vector<int32_t> dst_len;
+    int64_t units = 0, n_dst = 0, fresh_used = 0, app_total = 0, all_new = 0;
+    size_t o_un = 0, o_ip = 0, o_at = 0, o_as = 0, o_ak = 0, o_en = 0;
+  } splice_rec, alias_rec;
+  struct AttnRec {
+    size_t o_seq = 0, o_it = 0, o_gr = 0, n_items = 0, n_groups = 0, bytes = 0;
+    int32_t n_parts = 0;
+    int64_t total_q = 0;
+  } attn_rec, na_rec;
+  PlanKey na_key;                  // sa_segment_prefill_attn_noalloc: the plan na_host holds
+  bool na_valid = false;
   struct Stage {
     void* host = nullptr;
     size_t cap = 0;
@@ -143,6 +199,7 @@ sa_status upload_plan(sa_ctx* ctx, PlanKind kind, const PlanImage& img, hipStrea
                       uint8_t** dev) {
   sa_ctx::DevPlan& dp = ctx->plans[kind];
   const size_t n = img.bytes.size();
+  dp.key_valid = false;            // until the caller has noted what the buffer now holds
   if (dp.valid && dp.stream == (void*)stream && dp.shadow.size() == n &&
       memcmp(dp.shadow.data(), img.bytes.data(), n) == 0) {
     *dev = dp.dev;
@@ -437,16 +494,32 @@ sa_status sa_kv_append(sa_ctx* ctx, const sa_layout* layout, int32_t layer, void
     return fail(SA_ERR_SHAPE, "layer %d outside [0, %d)", layer, layout->num_layers);
   if (batch < 1) return fail(SA_ERR_SHAPE, "batch %d < 1", batch);
   if (!h_start || !h_new_len) return fail(SA_ERR_NULL, "h_start / h_new_len is NULL");
-  std::vector<int32_t> tok_begin(batch + 1);
-  int64_t total = 0;
-  for (int b = 0; b < batch; ++b) {
-    if (h_start[b] < 0 || h_new_len[b] < 0 || (int64_t)h_start[b] + h_new_len[b] > INT32_MAX)
-      return fail(SA_ERR_SHAPE, "sequence %d: start %d, new_len %d", b, h_start[b], h_new_len[b]);
-    tok_begin[b] = (int32_t)total;
-    total += h_new_len[b];
-    if (total > INT32_MAX / 2) return fail(SA_ERR_SHAPE, "too many new tokens");
+  // a call with the arrays of the last one passed these checks then
+  bool same = false;
+  sa_ctx::AppendRec rec;
+  if (ctx) {
+    sa_ctx::DevPlan& dp = ctx->plans[kPlanAppend];
+    dp.key.begin();
+    dp.key.add(h_start, (size_t)batch);
+    dp.key.add(h_new_len, (size_t)batch);
+    same = dp.reusable(dp.key.end(), (hipStream_t)stream) && !debug_checks();
+    if (!same) dp.key_valid = false;
+    rec = ctx->append_rec;
   }
-  tok_begin[batch] = (int32_t)total;
+  std::vector<int32_t> tok_begin;
+  if (!same) {
+    rec = sa_ctx::AppendRec{};
+    tok_begin.resize(batch + 1);
+    for (int b = 0; b < batch; ++b) {
+      if (h_start[b] < 0 || h_new_len[b] < 0 || (int64_t)h_start[b] + h_new_len[b] > INT32_MAX)
+        return fail(SA_ERR_SHAPE, "sequence %d: start %d, new_len %d", b, h_start[b], h_new_len[b]);
+      tok_begin[b] = (int32_t)rec.total;
+      rec.total += h_new_len[b];
+      if (rec.total > INT32_MAX / 2) return fail(SA_ERR_SHAPE, "too many new tokens");
+    }
+    tok_begin[batch] = (int32_t)rec.total;
+  }
+  const int64_t total = rec.total;
   if (!k_pool || !v_pool || !pages.indptr || !pages.indices)
     return fail(SA_ERR_NULL, "pool or page table pointer is NULL");
   if (total > 0 && (!k_new || !v_new)) return fail(SA_ERR_NULL, "k_new / v_new is NULL");
@@ -464,12 +537,16 @@ sa_status sa_kv_append(sa_ctx* ctx, const sa_layout* layout, int32_t layer, void
     if (s != SA_OK) return s;
   }
 
-  PlanImage img;
-  const size_t o_tok = img.add(tok_begin.data(), tok_begin.size());
-  const size_t o_start = img.add(h_start, (size_t)batch);
-  uint8_t* dev = nullptr;
-  s = upload_plan(ctx, kPlanAppend, img, (hipStream_t)stream, &dev);
-  if (s != SA_OK) return s;
+  uint8_t* dev = ctx->plans[kPlanAppend].dev;
+  if (!same) {
+    PlanImage img;
+    rec.o_tok = img.add(tok_begin.data(), tok_begin.size());
+    rec.o_start = img.add(h_start, (size_t)batch);
+    s = upload_plan(ctx, kPlanAppend, img, (hipStream_t)stream, &dev);
+    if (s != SA_OK) return s;
+    ctx->append_rec = rec;
+    ctx->plans[kPlanAppend].key_valid = true;
+  }
 
   sa::AppendArgs a{};
   const int64_t lo = (int64_t)layer * layer_elems(layout);
@@ -477,8 +554,8 @@ sa_status sa_kv_append(sa_ctx* ctx, const sa_layout* layout, int32_t layer, void
   a.v_pool = (uint16_t*)v_pool + lo;
   a.k_new = (const uint16_t*)k_new;
   a.v_new = (const uint16_t*)v_new;
-  a.tok_begin = (const int32_t*)(dev + o_tok);
-  a.start = (const int32_t*)(dev + o_start);
+  a.tok_begin = (const int32_t*)(dev + rec.o_tok);
+  a.start = (const int32_t*)(dev + rec.o_start);
   a.indptr = pages.indptr;
   a.indices = pages.indices;
   a.err = ctx->d_err;
@@ -501,6 +578,39 @@ sa_status sa_kv_append(sa_ctx* ctx, const sa_layout* layout, int32_t layer, void
 
 namespace {
 
+// Whether the device's plan of this kind was made from these arrays (the plan
+// depends on nothing else: the page size, the capacities it was checked
+// against, and the key-value heads and layers only at the launch).  Otherwise
+// the arrays are noted for the plan that is about to replace it; NULL arrays
+// and bad counts are left to the planner's checks.
+bool splice_same(sa_ctx* ctx, PlanKind kind, const sa_layout* layout, int32_t batch, const int32_t* h_src_len,
+                 const int32_t* h_keep_indptr, const int32_t* h_keep_spans, const int32_t* h_reserve,
+                 const int32_t* h_new_len, int32_t num_fresh, int32_t dst_capacity, hipStream_t stream) {
+  if (!ctx) return false;
+  sa_ctx::DevPlan& dp = ctx->plans[kind];
+  const bool had = dp.key_valid;
+  dp.key_valid = false;
+  std::string err;
+  if (!layout || sa::check_layout(layout, err) != SA_OK || batch < 1 || !h_src_len || !h_keep_indptr || !h_reserve ||
+      h_keep_indptr[0] != 0)
+    return false;
+  for (int b = 0; b < batch; ++b)
+    if (h_keep_indptr[b + 1] < h_keep_indptr[b]) return false;
+  if (h_keep_indptr[batch] > 0 && !h_keep_spans) return false;
+  const int32_t head[5] = {layout->page_size, batch, num_fresh, dst_capacity, h_new_len != nullptr};
+  dp.key.begin();
+  dp.key.add(head, 5);
+  dp.key.add(h_src_len, (size_t)batch);
+  dp.key.add(h_reserve, (size_t)batch);
+  dp.key.add(h_keep_indptr, (size_t)batch + 1);
+  if (h_keep_indptr[batch] > 0) dp.key.add(h_keep_spans, 2 * (size_t)h_keep_indptr[batch]);
+  if (h_new_len) dp.key.add(h_new_len, (size_t)batch);
+  const bool same = dp.key.end();
+  dp.key_valid = had;
+  if (dp.reusable(same, stream) && !debug_checks()) return true;
+  dp.key_valid = false;
+  return false;
+}
 
 // The copy splice, and with new_len non-NULL an append of new rows of layer
 // `layer` behind each sequence's kept tokens in the same launch.
@@ -510,19 +620,37 @@ sa_status splice_launch(sa_ctx* ctx, const sa_layout* layout, const void* k_src,
                         sa_pages src, const int32_t* d_fresh, int32_t num_fresh, int32_t* d_dst_indptr,
                         int32_t* d_dst_indices, int32_t dst_capacity, int32_t* h_dst_len, int32_t layer,
                         const void* k_new, const void* v_new, const int32_t* h_new_len, void* stream) {
-  sa::SplicePlan sp;
-  sa_status s = sa::plan_splice(layout, batch, h_src_len, h_keep_indptr, h_keep_spans, h_reserve, false, num_fresh,
-                                dst_capacity, sp, g_err);
-  if (s != SA_OK) return s;
-  if (!h_dst_len) return fail(SA_ERR_NULL, "h_dst_len is NULL");
-  const int64_t units = (int64_t)sp.units.size(), n_dst = sp.n_dst;
-  const int P = layout->page_size;
   const bool app = h_new_len != nullptr;
+  const int P = layout ? layout->page_size : 0;
+  sa_ctx::SpliceRec local;
+  bool same = splice_same(ctx, kPlanAssemble, layout, batch, h_src_len, h_keep_indptr, h_keep_spans, h_reserve,
+                          h_new_len, num_fresh, dst_capacity, (hipStream_t)stream);
+  sa::SplicePlan sp;
   sa::SpliceAppendPlan ap;
-  if (app) {
-    s = sa::plan_splice_append(layout, batch, h_new_len, layer, sp, ap, g_err);
+  sa_status s;
+  if (!same) {
+    s = sa::plan_splice(layout, batch, h_src_len, h_keep_indptr, h_keep_spans, h_reserve, false, num_fresh,
+                        dst_capacity, sp, g_err);
     if (s != SA_OK) return s;
-    if (ap.all_new > 0 && (!k_new || !v_new)) return fail(SA_ERR_NULL, "k_new / v_new is NULL");
+    local.units = (int64_t)sp.units.size();
+    local.n_dst = sp.n_dst;
+    local.dst_len = sp.dst_len;
+  }
+  if (!h_dst_len) return fail(SA_ERR_NULL, "h_dst_len is NULL");
+  if (app) {
+    if (layer < 0 || layer >= layout->num_layers)
+      return fail(SA_ERR_SHAPE, "layer %d outside [0, %d)", layer, layout->num_layers);
+    if (!same) {
+      s = sa::plan_splice_append(layout, batch, h_new_len, layer, sp, ap, g_err);
+      if (s != SA_OK) return s;
+      local.app_total = ap.total;
+      local.all_new = ap.all_new;
+    }
+  }
+  const sa_ctx::SpliceRec& rec = same ? ctx->splice_rec : local;
+  const int64_t units = rec.units, n_dst = rec.n_dst;
+  if (app) {
+    if (rec.all_new > 0 && (!k_new || !v_new)) return fail(SA_ERR_NULL, "k_new / v_new is NULL");
     if (!aligned16(k_new) || !aligned16(v_new)) return fail(SA_ERR_ALIGN, "new-row pointer not 16-byte aligned");
   }
   // the source slots are read only for surviving pages, the free list and the
@@ -538,25 +666,29 @@ sa_status splice_launch(sa_ctx* ctx, const sa_layout* layout, const void* k_src,
     s = debug_splice(sp, src, d_fresh, batch, layout->num_slots, false, (hipStream_t)stream);
     if (s != SA_OK) return s;
   }
-  memcpy(h_dst_len, sp.dst_len.data(), sizeof(int32_t) * batch);
+  memcpy(h_dst_len, rec.dst_len.data(), sizeof(int32_t) * batch);
 
-  PlanImage img;
-  const size_t o_un = img.add(sp.units.data(), sp.units.size());
-  const size_t o_ip = img.add(sp.dst_indptr.data(), sp.dst_indptr.size());
-  const size_t o_at = img.add(ap.tok_begin.data(), app ? ap.tok_begin.size() : 0);
-  const size_t o_as = img.add(ap.start.data(), app ? ap.start.size() : 0);
-  const size_t o_ak = img.add(ap.knew.data(), app ? ap.knew.size() : 0);
-  uint8_t* dev = nullptr;
-  s = upload_plan(ctx, kPlanAssemble, img, (hipStream_t)stream, &dev);
-  if (s != SA_OK) return s;
+  uint8_t* dev = ctx->plans[kPlanAssemble].dev;
+  if (!same) {
+    PlanImage img;
+    local.o_un = img.add(sp.units.data(), sp.units.size());
+    local.o_ip = img.add(sp.dst_indptr.data(), sp.dst_indptr.size());
+    local.o_at = img.add(ap.tok_begin.data(), app ? ap.tok_begin.size() : 0);
+    local.o_as = img.add(ap.start.data(), app ? ap.start.size() : 0);
+    local.o_ak = img.add(ap.knew.data(), app ? ap.knew.size() : 0);
+    s = upload_plan(ctx, kPlanAssemble, img, (hipStream_t)stream, &dev);
+    if (s != SA_OK) return s;
+    ctx->splice_rec = local;
+    ctx->plans[kPlanAssemble].key_valid = true;
+  }
 
   sa::AsmArgs a{};
   a.k_src = (const uint16_t*)k_src;
   a.v_src = (const uint16_t*)v_src;
   a.k_dst = (uint16_t*)k_dst;
   a.v_dst = (uint16_t*)v_dst;
-  a.units = (const sa::AsmUnit*)(dev + o_un);
-  a.dst_indptr = (const int32_t*)(dev + o_ip);
+  a.units = (const sa::AsmUnit*)(dev + rec.o_un);
+  a.dst_indptr = (const int32_t*)(dev + rec.o_ip);
   a.src_indptr = src.indptr;
   a.src_indices = src.indices;
   a.fresh = d_fresh;
@@ -575,10 +707,10 @@ sa_status splice_launch(sa_ctx* ctx, const sa_layout* layout, const void* k_src,
   if (app) {
     a.k_new = (const uint16_t*)k_new;
     a.v_new = (const uint16_t*)v_new;
-    a.app_tok_begin = (const int32_t*)(dev + o_at);
-    a.app_start = (const int32_t*)(dev + o_as);
-    a.app_knew = (const int32_t*)(dev + o_ak);
-    a.app_chunks = ap.total * layout->num_kv_heads * 16;
+    a.app_tok_begin = (const int32_t*)(dev + rec.o_at);
+    a.app_start = (const int32_t*)(dev + rec.o_as);
+    a.app_knew = (const int32_t*)(dev + rec.o_ak);
+    a.app_chunks = rec.app_total * layout->num_kv_heads * 16;
     a.app_blocks = (int32_t)((a.app_chunks + sa::kAsmThreads * sa::kAsmDepth - 1) / (sa::kAsmThreads * sa::kAsmDepth));
   }
   const int64_t table_blocks = (std::max<int64_t>(n_dst, batch + 1) + sa::kAsmThreads - 1) / sa::kAsmThreads;
@@ -626,13 +758,24 @@ sa_status sa_kv_splice_alias(sa_ctx* ctx, const sa_layout* layout, int32_t batch
                              const int32_t* d_fresh, int32_t num_fresh, int32_t* d_dst_indptr,
                              int32_t* d_dst_indices, int32_t dst_capacity, int32_t* h_dst_len,
                              void* stream) {
+  sa_ctx::SpliceRec local;
+  const bool same = splice_same(ctx, kPlanAlias, layout, batch, h_src_len, h_keep_indptr, h_keep_spans, h_reserve,
+                                nullptr, num_fresh, dst_capacity, (hipStream_t)stream);
   sa::SplicePlan sp;
-  sa_status s = sa::plan_splice(layout, batch, h_src_len, h_keep_indptr, h_keep_spans, h_reserve, true, num_fresh,
-                                dst_capacity, sp, g_err);
-  if (s != SA_OK) return s;
+  sa_status s;
+  if (!same) {
+    s = sa::plan_splice(layout, batch, h_src_len, h_keep_indptr, h_keep_spans, h_reserve, true, num_fresh,
+                        dst_capacity, sp, g_err);
+    if (s != SA_OK) return s;
+    local.units = (int64_t)sp.units.size();
+    local.n_dst = sp.n_dst;
+    local.fresh_used = sp.fresh_used;
+    local.dst_len = sp.dst_len;
+  }
+  const sa_ctx::SpliceRec& rec = same ? ctx->alias_rec : local;
   if (!h_dst_len) return fail(SA_ERR_NULL, "h_dst_len is NULL");
-  if (!src.indptr || !d_dst_indptr || (!sp.units.empty() && !src.indices) || (sp.n_dst > 0 && !d_dst_indices) ||
-      (sp.fresh_used > 0 && !d_fresh))
+  if (!src.indptr || !d_dst_indptr || (rec.units > 0 && !src.indices) || (rec.n_dst > 0 && !d_dst_indices) ||
+      (rec.fresh_used > 0 && !d_fresh))
     return fail(SA_ERR_NULL, "a device pointer is NULL");
   s = check_ctx(ctx);
   if (s != SA_OK) return s;
@@ -640,20 +783,24 @@ sa_status sa_kv_splice_alias(sa_ctx* ctx, const sa_layout* layout, int32_t batch
     s = debug_splice(sp, src, d_fresh, batch, layout->num_slots, true, (hipStream_t)stream);
     if (s != SA_OK) return s;
   }
-  memcpy(h_dst_len, sp.dst_len.data(), sizeof(int32_t) * batch);
+  memcpy(h_dst_len, rec.dst_len.data(), sizeof(int32_t) * batch);
 
-  PlanImage img;
-  const size_t o_un = img.add(sp.units.data(), sp.units.size());
-  const size_t o_ip = img.add(sp.dst_indptr.data(), sp.dst_indptr.size());
-  const size_t o_en = img.add(sp.entry.data(), sp.entry.size());
-  uint8_t* dev = nullptr;
-  s = upload_plan(ctx, kPlanAlias, img, (hipStream_t)stream, &dev);
-  if (s != SA_OK) return s;
+  uint8_t* dev = ctx->plans[kPlanAlias].dev;
+  if (!same) {
+    PlanImage img;
+    local.o_un = img.add(sp.units.data(), sp.units.size());
+    local.o_ip = img.add(sp.dst_indptr.data(), sp.dst_indptr.size());
+    local.o_en = img.add(sp.entry.data(), sp.entry.size());
+    s = upload_plan(ctx, kPlanAlias, img, (hipStream_t)stream, &dev);
+    if (s != SA_OK) return s;
+    ctx->alias_rec = local;
+    ctx->plans[kPlanAlias].key_valid = true;
+  }
 
   sa::AliasArgs a{};
-  a.units = (const sa::AsmUnit*)(dev + o_un);
-  a.entry = (const int32_t*)(dev + o_en);
-  a.dst_indptr = (const int32_t*)(dev + o_ip);
+  a.units = (const sa::AsmUnit*)(dev + rec.o_un);
+  a.entry = (const int32_t*)(dev + rec.o_en);
+  a.dst_indptr = (const int32_t*)(dev + rec.o_ip);
   a.src_indptr = src.indptr;
   a.src_indices = src.indices;
   a.fresh = d_fresh;
@@ -661,9 +808,9 @@ sa_status sa_kv_splice_alias(sa_ctx* ctx, const sa_layout* layout, int32_t batch
   a.out_indices = d_dst_indices;
   a.err = ctx->d_err;
   a.num_slots = layout->num_slots;
-  a.n_dst = (int32_t)sp.n_dst;
+  a.n_dst = (int32_t)rec.n_dst;
   a.B = batch;
-  const int64_t blocks = (std::max<int64_t>(sp.n_dst, batch + 1) + 255) / 256;
+  const int64_t blocks = (std::max<int64_t>(rec.n_dst, batch + 1) + 255) / 256;
   launch_timed(sa::splice_alias_kernel, dim3((unsigned)blocks), dim3(256), (hipStream_t)stream,
                ctx->kernel_ev[SA_TIMED_PAGES], a);
   SA_HIP(hipGetLastError());
@@ -690,10 +837,29 @@ sa_status attn_launch(sa_ctx* ctx, const sa_layout* layout, int32_t layer, const
                       const void* v_new, int32_t batch, const int32_t* h_q_len, const int32_t* h_kv_len,
                       sa_pages pages, float softmax_scale, void* o, float* lse, void* stream,
                       bool noalloc = false) {
+  const AttnVariant var = attn_variant();
   std::vector<sa::SeqDesc> seqs;
-  int64_t total_q = 0;
-  sa_status s = sa::plan_attn_check(layout, layer, batch, h_q_len, h_kv_len, softmax_scale, seqs, total_q, g_err);
-  if (s != SA_OK) return s;
+  // a call with the heads and lengths of the last one has its plan on the
+  // device already, and its lengths passed the checks then
+  bool same = false;
+  if (ctx && layout && sa::check_attn_call(layout, layer, batch, h_q_len, h_kv_len, softmax_scale, g_err) == SA_OK) {
+    sa_ctx::DevPlan& dp = ctx->plans[kPlanAttn];
+    PlanKey& key = noalloc ? ctx->na_key : dp.key;
+    const int32_t head[3] = {layout->num_q_heads, layout->num_kv_heads, batch};
+    key.begin();
+    key.add(head, 3);
+    key.add(h_q_len, (size_t)batch);
+    key.add(h_kv_len, (size_t)batch);
+    const bool equal = key.end();
+    same = noalloc ? equal && ctx->na_valid : dp.reusable(equal, (hipStream_t)stream);
+    if (!same) (noalloc ? ctx->na_valid : dp.key_valid) = false;
+  }
+  int64_t total_q = same ? (noalloc ? ctx->na_rec : ctx->attn_rec).total_q : 0;
+  sa_status s;
+  if (!same) {
+    s = sa::plan_attn_check(layout, layer, batch, h_q_len, h_kv_len, softmax_scale, seqs, total_q, g_err);
+    if (s != SA_OK) return s;
+  }
   const int Hq = layout->num_q_heads, Hkv = layout->num_kv_heads, G = Hq / Hkv;
   if (total_q > 0 && (!q || !o)) return fail(SA_ERR_NULL, "q / o is NULL");
   if (!k_pool || !v_pool || !pages.indptr || !pages.indices)
@@ -709,7 +875,6 @@ sa_status attn_launch(sa_ctx* ctx, const sa_layout* layout, int32_t layer, const
   if (total_q == 0) return SA_OK;
 
   // ---- kernel variant: query rows per wave (32 * qt) and waves per work item
-  const AttnVariant var = attn_variant();
   const bool exact = ctx->exact_scale && var.pipe == 1;
   const bool pool_rsrc = layer_elems(layout) * 2 < ((int64_t)1 << 31);
   const int64_t new_bytes = total_q * Hkv * sa::kHD * 2;
@@ -735,17 +900,27 @@ sa_status attn_launch(sa_ctx* ctx, const sa_layout* layout, int32_t layer, const
   }
   const int rows_item = 32 * var.qt * var.waves;
 
-  sa::AttnShape shape;
-  shape.rows_item = rows_item;
-  shape.num_cu = ctx->num_cu;
-  shape.pair_rounds = var.pipe != 2;      // the two-group kernel runs one block per CU
-  const size_t part_bytes = (size_t)rows_item * (sa::kHD + 1) * sizeof(float);   // one key-range part
-  if (noalloc) shape.max_parts = (int64_t)((kNoAllocBytes - kNoAllocPlanBytes) / part_bytes);
-  sa::AttnPlan plan;
-  sa::plan_attn_items(layout, seqs, shape, &ctx->xcd, plan);
-  std::vector<sa::AttnItem>& items = plan.items;
-  std::vector<sa::MergeGroup>& groups = plan.groups;
-  const int32_t n_parts = plan.n_parts;
+  sa_ctx::AttnRec& rec = noalloc ? ctx->na_rec : ctx->attn_rec;
+  PlanImage img;
+  if (!same) {
+    sa::AttnShape shape;
+    shape.rows_item = rows_item;
+    shape.num_cu = ctx->num_cu;
+    shape.pair_rounds = var.pipe != 2;      // the two-group kernel runs one block per CU
+    const size_t part_bytes = (size_t)rows_item * (sa::kHD + 1) * sizeof(float);   // one key-range part
+    if (noalloc) shape.max_parts = (int64_t)((kNoAllocBytes - kNoAllocPlanBytes) / part_bytes);
+    sa::AttnPlan plan;
+    sa::plan_attn_items(layout, seqs, shape, &ctx->xcd, plan);
+    rec.n_items = plan.items.size();
+    rec.n_groups = plan.groups.size();
+    rec.n_parts = plan.n_parts;
+    rec.total_q = total_q;
+    rec.o_seq = img.add(seqs.data(), seqs.size());
+    rec.o_it = img.add(plan.items.data(), plan.items.size());
+    rec.o_gr = img.add(plan.groups.data(), plan.groups.size());
+    rec.bytes = img.bytes.size();
+  }
+  const int32_t n_parts = rec.n_parts;
 
   if (n_parts > 0 && !noalloc) {
     const size_t need = (size_t)n_parts * rows_item * (sa::kHD + 1) * sizeof(float);
@@ -758,33 +933,33 @@ sa_status attn_launch(sa_ctx* ctx, const sa_layout* layout, int32_t layer, const
     }
   }
 
-  PlanImage img;
-  const size_t o_seq = img.add(seqs.data(), seqs.size());
-  const size_t o_it = img.add(items.data(), items.size());
-  const size_t o_gr = img.add(groups.data(), groups.size());
-  uint8_t* dev = nullptr;
+  uint8_t* dev = ctx->plans[kPlanAttn].dev;
   float* part = ctx->part;
   if (noalloc) {
-    // the plan goes to the front of the fixed scratch, through pinned staging
-    // whose previous copy must have been read first; the partials follow it
-    const size_t n = img.bytes.size();
-    if (n > kNoAllocPlanBytes)
+    // the plan goes to the front of the fixed scratch on every call (other
+    // contexts use the same array), through pinned staging whose previous copy
+    // must have been read before a new plan is put there; the partials follow it
+    if (rec.bytes > kNoAllocPlanBytes)
       return fail(SA_ERR_SHAPE, "the launch's plan needs %zu bytes; the fixed scratch of the allocation-free "
-                  "entry point holds %zu (about %zu work items)", n, kNoAllocPlanBytes,
+                  "entry point holds %zu (about %zu work items)", rec.bytes, kNoAllocPlanBytes,
                   kNoAllocPlanBytes / sizeof(sa::AttnItem));
-    if (ctx->na_pending) {
-      SA_HIP(hipEventSynchronize(ctx->na_ev));
-      ctx->na_pending = false;
+    if (!same) {
+      if (ctx->na_pending) {
+        SA_HIP(hipEventSynchronize(ctx->na_ev));
+        ctx->na_pending = false;
+      }
+      memcpy(ctx->na_host, img.bytes.data(), rec.bytes);
+      ctx->na_valid = true;
     }
-    memcpy(ctx->na_host, img.bytes.data(), n);
-    SA_HIP(hipMemcpyAsync(ctx->scratch, ctx->na_host, n, hipMemcpyHostToDevice, (hipStream_t)stream));
+    SA_HIP(hipMemcpyAsync(ctx->scratch, ctx->na_host, rec.bytes, hipMemcpyHostToDevice, (hipStream_t)stream));
     SA_HIP(hipEventRecord(ctx->na_ev, (hipStream_t)stream));
     ctx->na_pending = true;
     dev = ctx->scratch;
     part = (float*)(ctx->scratch + kNoAllocPlanBytes);
-  } else {
+  } else if (!same) {
     s = upload_plan(ctx, kPlanAttn, img, (hipStream_t)stream, &dev);
     if (s != SA_OK) return s;
+    ctx->plans[kPlanAttn].key_valid = true;
   }
 
   sa::AttnArgs a{};
@@ -796,13 +971,13 @@ sa_status attn_launch(sa_ctx* ctx, const sa_layout* layout, int32_t layer, const
   a.lse = lse;
   a.part_o = n_parts > 0 ? part : nullptr;
   a.part_lse = n_parts > 0 ? part + (size_t)n_parts * rows_item * sa::kHD : nullptr;
-  a.items = (const sa::AttnItem*)(dev + o_it);
-  a.seqs = (const sa::SeqDesc*)(dev + o_seq);
+  a.items = (const sa::AttnItem*)(dev + rec.o_it);
+  a.seqs = (const sa::SeqDesc*)(dev + rec.o_seq);
   a.indptr = pages.indptr;
   a.indices = pages.indices;
   a.err = ctx->d_err;
   a.num_slots = (int32_t)layout->num_slots;
-  a.n_items = (int32_t)items.size();
+  a.n_items = (int32_t)rec.n_items;
   a.Hq = Hq;
   a.Hkv = Hkv;
   a.G = G;
@@ -813,26 +988,26 @@ sa_status attn_launch(sa_ctx* ctx, const sa_layout* layout, int32_t layer, const
     a.new_bytes = (uint32_t)new_bytes;
   }
   if (ctx->blk_clock != nullptr && var.pipe == 1) {
-    if ((int64_t)items.size() > ctx->blk_clock_cap)
+    if ((int64_t)rec.n_items > ctx->blk_clock_cap)
       return fail(SA_ERR_SHAPE, "block clock buffer holds %lld blocks, the launch has %zu",
-                  (long long)ctx->blk_clock_cap, items.size());
+                  (long long)ctx->blk_clock_cap, rec.n_items);
     a.blk_clock = ctx->blk_clock;
   }
-  launch_attn(layout->page_size, var, pool_rsrc, exact, fused, dim3((unsigned)items.size()), (hipStream_t)stream,
+  launch_attn(layout->page_size, var, pool_rsrc, exact, fused, dim3((unsigned)rec.n_items), (hipStream_t)stream,
               ctx->kernel_ev[SA_TIMED_ATTN], a);
   SA_HIP(hipGetLastError());
-  if (!groups.empty()) {
+  if (rec.n_groups > 0) {
     sa::MergeArgs m{};
     m.part_o = a.part_o;
     m.part_lse = a.part_lse;
-    m.groups = (const sa::MergeGroup*)(dev + o_gr);
+    m.groups = (const sa::MergeGroup*)(dev + rec.o_gr);
     m.seqs = a.seqs;
     m.o = a.o;
     m.lse = lse;
     m.Hq = Hq;
     m.G = G;
     m.rows = rows_item;
-    hipLaunchKernelGGL(sa::merge_kernel, dim3((unsigned)groups.size(), (unsigned)((rows_item + 31) / 32)), dim3(256), 0,
+    hipLaunchKernelGGL(sa::merge_kernel, dim3((unsigned)rec.n_groups, (unsigned)((rows_item + 31) / 32)), dim3(256), 0,
                        (hipStream_t)stream, m);
     SA_HIP(hipGetLastError());
   }
@@ -913,6 +1088,7 @@ sa_status sa_set_kernel_events(sa_ctx* ctx, int32_t which, void* start_event, vo
 sa_status sa_set_xcd_weights(sa_ctx* ctx, const float* h_speed) {
   sa_status s = check_ctx(ctx);
   if (s != SA_OK) return s;
+  ctx->plans[kPlanAttn].key_valid = ctx->na_valid = false;   // other speeds, another placement
   if (h_speed == nullptr) {
     ctx->xcd = sa::XcdState{};
     return SA_OK;
