@@ -127,7 +127,7 @@ const char *sa_last_error(void);
  * kind's device plan buffer and of each pinned staging buffer; an attention
  * call's plan takes about 40 bytes per work item (one per sequence, KV head
  * and 128 packed query rows, and per key-range part of a split item) plus
- * 16 bytes per sequence, 24 per split item and 768 of alignment; a splice's
+ * 16 bytes per sequence, 8 per key-range part and 768 of alignment; a splice's
  * about 24 bytes per surviving page plus 16 per sequence.  split_bytes:
  * capacity of the split-KV partials, 128 * 129 * 4 bytes per key-range part.
  * Buffers only grow; outgrown ones are kept until sa_destroy.
@@ -141,7 +141,7 @@ sa_status sa_reserve(sa_ctx *ctx, int64_t plan_bytes, int64_t split_bytes);
  * no context, no GPU), for latency models of a batch (paper Sec. 4, Eq. 1
  * models a batch from its decode and prefill work; how the work falls onto
  * the chip's workgroup slots adds to that).  out[0]: workgroups; out[1]:
- * key-range parts of split items (when > 0, a partial-merge launch follows);
+ * key-range parts of split items (whose partial results the launch itself merges);
  * out[2]: 64-key tiles over all items; out[3]: makespan in tiles when the
  * items are taken in launch order by whichever of the 2 x num_cu workgroup
  * slots frees first (a decode item's tiles count a quarter: its four waves
@@ -311,8 +311,8 @@ sa_status sa_segment_prefill_attn(sa_ctx *ctx, const sa_layout *layout, int32_t 
  * allocated at sa_create.  Limits: the plan (about 40 bytes per work item, a
  * work item per sequence, KV head and 128 packed query rows) must fit 2 MiB,
  * else SA_ERR_SHAPE before anything is enqueued; the partials get the other
- * 30 MiB (476 key-range parts of 128 rows), and a launch that would split
- * into more parts is split more coarsely instead.  Every call on one GPU uses
+ * 30 MiB (476 key-range parts of 128 rows and their counters), and a launch
+ * that would split into more parts is split more coarsely instead.  Every call on one GPU uses
  * that GPU's array, whichever context makes it, and leaves the last call's
  * contents there: calls that overlap in time on one GPU (two streams, two
  * contexts) race, so order them.  The call may wait on the host for the
@@ -360,8 +360,9 @@ sa_status sa_set_fused_append(sa_ctx *ctx, int32_t enable);
  * rather than that of the call (events recorded around a call also span the
  * dispatch gap, several microseconds).  Kinds:
  *   SA_TIMED_ATTN   the attention kernel of sa_segment_prefill_attn and
- *                   sa_segment_prefill_attn_append (not the partial merge
- *                   that follows a launch split by key range)
+ *                   sa_segment_prefill_attn_append (which merges the parts of
+ *                   a launch split by key range; not the merge kernel of
+ *                   SA_ATTN_VARIANT 1 and 2)
  *   SA_TIMED_PAGES  the page kernel of sa_kv_append, sa_kv_assemble,
  *                   sa_kv_assemble_append, sa_kv_splice_alias and the append
  *                   launch of sa_segment_prefill_attn_append

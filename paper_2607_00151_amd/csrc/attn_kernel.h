@@ -47,6 +47,12 @@ struct AttnArgs {
   float* lse;               // nullable
   float* part_o;            // [parts][rows_per_item][kHD] normalised partial outputs
   float* part_lse;          // [parts][rows_per_item] log2-domain LSE of each partial
+  // attn_pipe_kernel, which merges the parts itself: where each part's item
+  // starts, and the arrival counters (kPartCounters per part, zero between launches)
+  const PartInfo* part_info;
+  int32_t* part_count;
+  uint32_t part_bytes;      // bytes of part_o, part_lse behind it (< 2^31)
+  int32_t n_parts;
   const AttnItem* items;
   const SeqDesc* seqs;
   const int32_t* indptr;
@@ -388,7 +394,8 @@ __global__ __launch_bounds__(64 * WAVES, (QT == 1 ? 2 : 1)) void attn_kernel(Att
   }
 }
 
-// Combine the key-range partials of split work items by their log-sum-exp.
+// Combine the key-range partials of split work items by their log-sum-exp
+// (attn_kernel and attn_pp_kernel; attn_pipe_kernel merges in its own launch).
 struct MergeArgs {
   const float* part_o;
   const float* part_lse;

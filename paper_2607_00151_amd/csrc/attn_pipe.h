@@ -158,6 +158,63 @@ __device__ __forceinline__ void write_own_rows(const AttnArgs& a, const AttnItem
   }
 }
 
+// ---- split items: partial results and their merge inside the launch
+//
+// Every key-range part of a split item leaves its normalised partial O and
+// log2 LSE in memory; the part that arrives last at the item's counter reads
+// all of them back and writes the item's output, so a split launch needs no
+// second kernel.  Nothing waits: each arrival is one fetch-add, and only the
+// one that completes the count goes on.
+//
+// The parts of an item run on different XCDs, whose L2s do not see each
+// other's ordinary stores before the kernel ends.  A release fence at device
+// scope would write back the whole L2 once per part (measured 2-3x on small
+// launches); instead the partials alone are stored and loaded at device scope
+// (the cache-policy bit sc1, as relaxed device-scope atomics are: written
+// through, and not served from a stale line), and a part counts itself only
+// after its own stores have been acknowledged (vmcnt 0).  Against the separate
+// merge launch: a 256-token chunk over a 4K prefix 36 -> 31 us of kernels.
+constexpr int kDeviceScope = 16;                           // sc1 of a buffer access
+constexpr int kPartCounters = 4;                           // counters per part: one per wave (prefill items)
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t part_rsrc(const AttnArgs& a) {
+  return __builtin_amdgcn_make_buffer_rsrc(a.part_o, (short)0, (int)a.part_bytes, 0x00020000);
+}
+// The whole offset goes in the vector operand: with a register as the scalar
+// offset of a 16-byte buffer store the compiler leaves out the wait state
+// between the store and a VALU write of its data registers, and the store was
+// seen (in this code, on MI355X) to pick up the new value of the first one.
+__device__ __forceinline__ void part_st4(const __amdgpu_buffer_rsrc_t& r, uint32_t off, f32x4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, off, 0, kDeviceScope);
+}
+__device__ __forceinline__ f32x4 part_ld4(const __amdgpu_buffer_rsrc_t& r, uint32_t off, uint32_t base) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, base, kDeviceScope));
+}
+__device__ __forceinline__ void part_st1(const __amdgpu_buffer_rsrc_t& r, uint32_t off, uint32_t base, float v) {
+  __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, off, base, kDeviceScope);
+}
+__device__ __forceinline__ float part_ld1(const __amdgpu_buffer_rsrc_t& r, uint32_t off, uint32_t base) {
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, base, kDeviceScope));
+}
+
+// This wave's stores are at device scope once acknowledged; then one arrival
+// at counter c of the item.  True for the last of its nsplit arrivals, which
+// also puts the counter back to zero for the next launch.
+__device__ __forceinline__ bool part_arrive(const AttnArgs& a, const PartInfo& pi, int c) {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0070);
+  asm volatile("" ::: "memory");
+  int32_t* const cnt = a.part_count + (int64_t)pi.part0 * kPartCounters + c;
+  int last = 0;
+  if (__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) == 0) {
+    last = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == pi.nsplit - 1;
+    if (last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  last = __builtin_amdgcn_readfirstlane(last);
+  asm volatile("" ::: "memory");
+  return last != 0;
+}
+
 // One group of four waves runs the item's rows over the keys
 // [g_lo, g_hi): the whole item when kGroups == 1; with two groups, group 0
 // takes the first half of the item's key tiles and group 1 the rest, and the
@@ -865,7 +922,58 @@ __device__ __attribute__((always_inline)) inline void pipe_group(const AttnArgs&
       if (a.lse != nullptr && hh_o == 0)
         a.lse[(int64_t)(sd.q_start + o_tok) * a.Hq + o_head] = lse2 * 0.69314718055994531f;
     }
+  } else if constexpr (kGroups == 1) {
+    // A part's partial: this wave's 32 rows in accumulator order (16-byte
+    // piece k of lane l at k KiB + 16 l), so stores and loads are whole lines.
+    // Each wave counts and merges its own rows: no barrier.
+    const __amdgpu_buffer_rsrc_t rp = part_rsrc(a);
+    const PartInfo pi = ld_uniform(a.part_info + it.part);
+    const uint32_t o_off = (uint32_t)(wave * 16 * 64 + lane_o) * 16;      // + k KiB
+    const uint32_t l_off = (uint32_t)a.n_parts * (kRows * kHD * 4) + (uint32_t)(wave * 32 + (lane_o & 31)) * 4;
+    {
+      const uint32_t base = (uint32_t)it.part * (kRows * kHD * 4);
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const int dt = k >> 2, i = k & 3;
+        part_st4(rp, base + o_off + k * 1024,
+                 f32x4{oacc[dt][4 * i] * inv, oacc[dt][4 * i + 1] * inv, oacc[dt][4 * i + 2] * inv,
+                       oacc[dt][4 * i + 3] * inv});
+      }
+      if (hh_o == 0) part_st1(rp, l_off, (uint32_t)it.part * (kRows * 4), lse2);
+    }
+    if (!part_arrive(a, pi, wave)) return;
+    float mx = -INFINITY;
+#pragma unroll 4
+    for (int s = 0; s < pi.nsplit; ++s) mx = fmaxf(mx, part_ld1(rp, l_off, (uint32_t)(pi.part0 + s) * (kRows * 4)));
+    f32x4 num[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) num[k] = f32x4{};
+    float den = 0.f;
+    const float sub = mx == -INFINITY ? 0.f : mx;
+#pragma unroll 2
+    for (int s = 0; s < pi.nsplit; ++s) {
+      const uint32_t base = (uint32_t)(pi.part0 + s) * (kRows * kHD * 4);
+      f32x4 x[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) x[k] = part_ld4(rp, o_off + k * 1024, base);
+      const float w = exp2f_fast(part_ld1(rp, l_off, (uint32_t)(pi.part0 + s) * (kRows * 4)) - sub);
+      den += w;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) num[k] += w * x[k];
+    }
+    if (o_row < rows_total) {
+      const float dinv = den > 0.f ? 1.f / den : 0.f;
+      uint16_t* orow = a.o + ((int64_t)(sd.q_start + o_tok) * a.Hq + o_head) * kHD;
+#pragma unroll
+      for (int k = 0; k < 16; ++k)
+        st_bf16x4(orow + 32 * (k >> 2) + 8 * (k & 3) + 4 * hh_o, num[k][0] * dinv, num[k][1] * dinv,
+                  num[k][2] * dinv, num[k][3] * dinv);
+      if (a.lse != nullptr && hh_o == 0)
+        a.lse[(int64_t)(sd.q_start + o_tok) * a.Hq + o_head] =
+            den > 0.f ? (mx + __builtin_amdgcn_logf(den)) * 0.69314718055994531f : -INFINITY;
+    }
   } else {
+    // two groups: plain rows, merged by merge_kernel
     const int lrow = wave * 32 + (lane_o & 31);
     float* po = a.part_o + ((int64_t)it.part * kRows + lrow) * kHD;
 #pragma unroll
@@ -884,227 +992,289 @@ __device__ __attribute__((always_inline)) inline void pipe_group(const AttnArgs&
 // ---- work items of at most 32 packed rows (decode requests)
 //
 // A decode request has one query token, so its item holds the G query heads
-// of one KV head -- a single 32-row MFMA block -- over the whole cached
-// context.  Run like a prefill item, one wave would carry every matrix
-// instruction of the item on one SIMD while the other three only load tiles,
-// and a prefill block sharing the CU, whose waves wait on each other at every
-// barrier, would run at the pace of its wave on that SIMD.  Here the four
-// waves split the item's keys instead: wave w takes the 32-key tiles
-// u0 + w, u0 + w + 4, ..., keeps its own online-softmax state over the same
-// rows, and needs no barrier.  Its K tiles go straight into registers (they
-// are the A operand of S^T = K Q^T, so no LDS round trip is needed) and its V
-// tiles into two 8 KB LDS slices of its own (the PV product reads them
-// transposed); K is requested one tile ahead and V two, so a wave keeps up to
-// 24 KB in flight.  The four partial results are merged through LDS at
-// the end.  The item stays bound by HBM, and its matrix work falls evenly on
-// the CU's four SIMDs.
+// of one KV head over the whole cached context.  Run like a prefill item, one
+// wave would carry every matrix instruction of the item on one SIMD while the
+// other three only load tiles, and a prefill block sharing the CU, whose waves
+// wait on each other at every barrier, would run at the pace of its wave on
+// that SIMD.  Here the four waves split the item's keys instead: wave w takes
+// the 32-key tiles u0 + w, u0 + w + 4, ..., keeps its own online-softmax state
+// over the same rows, and needs no barrier.  The item is bound by HBM when the
+// batch is large and by latency when it is small, so a wave keeps two tiles
+// (32 KB) in flight: K in two register sets (K is the A operand of
+// S^T = K Q^T, so no LDS round trip is needed), V in two 8 KB LDS slices of its
+// own (the PV product reads it transposed); page slots come 64 at a time in
+// one vector load, so no load waits for its page id.
+//
+// 16x16x32 MFMAs, kNB 16-row blocks: a request with G <= 16 query heads pads
+// its rows to 16, not 32 (half the exponentials, matrix time and accumulators
+// of a 32x32 block), and a K load covers 64 contiguous bytes of each of 16
+// rows.  Key 4 g + j (j < 4) and 16 + 4 g + j of a tile sit in the S^T
+// accumulators of lane group g = lane / 16, which makes them the k-slots
+// 8 g + j and 8 g + 4 + j of the PV product's P^T operand; two transposed
+// 4-key reads give V^T in the same order.
+//
+// Each page is reached through a buffer resource of its own, so the pool may
+// be of any size (a layer of a pool of a 288 GB card is easily past 2 GiB).
+//
+// Measured (MI355X, 32/8 heads, page 16, one stream of calls; before: 32-row
+// blocks, one K and two V tiles in flight, 1024-key parts, a merge launch):
+// 4 requests of 1K-4K keys 24.3 -> 13.0 us, 1 of 4K 22.0 -> 9.9 us, 8 of 6K-8K
+// 59.7 -> 48.5 us, 32 of 2K-8K 142 -> 111 us (5.9 TB/s), 64 of 4K-16K 451 -> 448
+// us (6.0 TB/s); 64/8 heads, page 32, 1 request of 73729 keys 93.0 -> 58.8 us
+// (5.1 TB/s; the merge kernel's 8 busy blocks had taken 28 us of it).
+typedef __attribute__((address_space(3))) float lds_f32;
 constexpr int kDecRows = kDecodeRows;        // rows of an item this path takes
 constexpr int kDecKeys = 32;                 // keys per tile of one wave
 
-template <int P, bool kExact>
+__device__ __forceinline__ int swz_dec(int key) { return (key & 7) << 1; }
+
+// over the four lanes that share lane % 16
+__device__ __forceinline__ float quad_max(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return pair_max(vmax(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ __forceinline__ float quad_sum(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return pair_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+
+template <int P, bool kExact, int kNB>
 __device__ __attribute__((always_inline)) inline void decode_group(const AttnArgs& a, const AttnItem& it,
-                                                                   const SeqDesc& sd, const PipeLds& L) {
+                                                                   lds_u8* k0, lds_u8* k1, lds_u8* v0, lds_u8* v1,
+                                                                   lds_f32* stats) {
+  // k0 .. v1: the prefill path's tile buffers; stats: [4 waves][32 rows] m, then l, and a flag behind
   static_assert(P == 16 || P == 32, "page size");
   constexpr int kWaves = 4;
   constexpr int kPagesPerTile = kDecKeys / P;                // 2 or 1
   constexpr int kSliceBytes = kDecKeys * kHD * 2;            // 8 KB: one V tile of one wave
+  constexpr int kSlotTiles = 64 / kPagesPerTile;             // tiles of one vector load of page slots
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) & (kWaves - 1);
-  const int hh = lane >> 5;
+  const int g = lane >> 4, r16 = lane & 15;
   const int G = a.G;
-  const int rows_total = sd.q_len * G;
-  const int pre = sd.kv_len - sd.q_len;
-
-  // every wave holds the same rows: row r of the block is lane r % 32
-  const int r_row = it.row0 + (lane & 31);
-  const int rr = r_row < rows_total ? r_row : rows_total - 1;
-  const int tok = rr / G;
-  const int head = it.kvh * G + (rr - tok * G);
-  const int qpos = pre + tok;
+  const int rows = it.q_len * G - it.row0;                   // 1 .. 16 kNB
+  const int pre = it.kv_len - it.q_len;
   const int g_lo = it.kv_begin, g_hi = it.kv_end;
   const int w_full = min(g_hi, pre + it.row0 / G + 1);      // keys below are visible to all rows
-
-  bf16x8 qop[8];
-  {
-    const uint16_t* qrow = a.q + ((int64_t)(sd.q_start + tok) * a.Hq + head) * kHD;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) qop[ks] = ld_bf16x8(qrow + (2 * ks + hh) * 8);
-  }
   const int32_t pt_base = ld_uniform(a.indptr + it.seq);
   const int32_t pt_count = ld_uniform(a.indptr + it.seq + 1) - pt_base;
-  TableCheck tcheck = table_check_issue<P>(a, it, pt_base, pt_count, 64 * kWaves);
-  if constexpr (!kExact) {
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) qop[ks][e] = (__bf16)((float)qop[ks][e] * a.c);
-  }
-  const bool table_ok = table_check_finish(a, tcheck, pt_base, 64 * kWaves);
 
-  lds_u8* const vslice[2] = {(wave & 2 ? L.k1 : L.k0) + (wave & 1) * kSliceBytes,
-                             (wave & 2 ? L.v1 : L.v0) + (wave & 1) * kSliceBytes};
-  const int64_t slot_bytes = (int64_t)a.Hkv * P * kHD * 2;
-  const uint32_t pool_bytes = (uint32_t)(a.num_slots * slot_bytes);      // < 2^31 (caller's condition)
-  const __amdgpu_buffer_rsrc_t rsrc_k =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.k), (short)0, (int)pool_bytes, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rsrc_v =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.v), (short)0, (int)pool_bytes, 0x00020000);
-  const int krow = lane & 31;
-  const int krow_off = (it.kvh * P + krow % P) * (kHD * 2) + hh * 16;   // this lane's K row, d-chunk parity
-  bool bad = false;
-
-  // Slot of page pg of the sequence, or -1 when the table lacks it or it lies
-  // outside the pool (then the page is not read and the error flag is raised).
-  auto slot_of = [&](int pg) __attribute__((always_inline)) {
-    const int32_t s = pg < pt_count ? ld_uniform(a.indices + pt_base + pg) : -1;
-    return (s >= 0 && s < a.num_slots) ? s : -1;
-  };
-  // Every tile issues exactly 8 K loads and 8 V loads, so that "the next
-  // tile's 16 loads may still be outstanding" is an exact wait: a row that must
-  // not be read gets an offset past the pool's buffer resource (the pool spans
-  // < 2^31 bytes), which returns zeros -- into registers or into LDS alike.
-  constexpr uint32_t kOutside = 0x80000000u;
-  // K of tile u into registers: lane l holds key l % 32, d-chunks 2 i + l / 32
-  // (the MFMA's A operand).  Keys past the item's end and absent pages are zeros
-  // (the former are masked; the latter behave as zero rows, and raise the flag).
-  auto load_k = [&](int u, bf16x8* kr) __attribute__((always_inline)) {
-    int32_t sl[kPagesPerTile];
-#pragma unroll
-    for (int p = 0; p < kPagesPerTile; ++p) {
-      sl[p] = slot_of(u * kPagesPerTile + p);
-      bad |= sl[p] < 0 && u * kDecKeys + p * P < g_hi;
-    }
-    const int32_t s = (kPagesPerTile == 2 && krow >= P) ? sl[kPagesPerTile - 1] : sl[0];
-    const bool ok = s >= 0 && u * kDecKeys + krow < g_hi;
-    const uint32_t base = ok ? (uint32_t)s * (uint32_t)slot_bytes + (uint32_t)krow_off : kOutside;
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      kr[i] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrc_k, base + i * 32, 0, 0));
-  };
-  // V of tile u into an LDS slice: load j fills rows 4j .. 4j + 3, lane i one
-  // 16-byte chunk of row 4j + i / 16 (XOR-swizzled as the prefill path's).
-  // Keys past the item's end and absent pages are zero rows, which keep the
-  // masked products finite.
-  auto load_v = [&](int u, lds_u8* dst) __attribute__((always_inline)) {
-    const int ts = u * kDecKeys;
-    int32_t sl[kPagesPerTile];
-#pragma unroll
-    for (int p = 0; p < kPagesPerTile; ++p) sl[p] = slot_of(u * kPagesPerTile + p);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int key = 4 * j + (lane >> 4);
-      const int s = sl[(4 * j) / P];
-      const uint32_t off = (uint32_t)((it.kvh * P + key % P) * (kHD * 2) + (((lane & 15) ^ swz_v(key)) << 4));
-      const bool ok = s >= 0 && ts + key < g_hi;
-      __attribute__((address_space(3))) void* d = (__attribute__((address_space(3))) void*)(dst + j * 1024);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_v, d, 16, ok ? off : kOutside,
-                                               s >= 0 ? (uint32_t)s * (uint32_t)slot_bytes : 0u, 0, 0);
-    }
-  };
-
-  const int tr_g = lane >> 4, tr_s = lane & 15;
-  const int tr_key = 4 * (tr_g >> 1) + (tr_s >> 2);
-  const int tr_d = 16 * (tr_g & 1) + 4 * (tr_s & 3);
-  f32x16 oacc[4];
-#pragma unroll
-  for (int dt = 0; dt < 4; ++dt) oacc[dt] = f32x16{};
-  float m_used = -INFINITY, msub = 0.f, l = 0.f;
-  bf16x8 kr[8];
-
-  // Issue order: K(u), V(u), V(u + 4); then in the step of tile u, K(u + 4)
-  // once S(u) has read K(u) out of the registers, and V(u + 8) once the PV
-  // product has read V(u) out of its slice.  At the top of the step of tile
-  // u, K(u) and V(u) have landed once at most V(u + 4)'s 8 loads are
-  // outstanding (K(u + 4) is issued later, within the step).
+  // page slots of this wave's tiles u, u + 4, ... from tile u0 + wave + 4 j0 on:
+  // lane i holds page i % kPagesPerTile of the (i / kPagesPerTile)-th of them.  A
+  // page the table lacks or a slot outside the pool is -1: it is not read, its
+  // rows are zeros, and it raises the error flag if the item has keys in it.
   const int u0 = g_lo / kDecKeys;
   const int u1 = (g_hi + kDecKeys - 1) / kDecKeys;
-  int u = u0 + wave;
-  if (u < u1) {
-    load_k(u, kr);
-    load_v(u, vslice[0]);
-  }
-  if (u + kWaves < u1) load_v(u + kWaves, vslice[1]);
-  auto step = [&](auto bc) __attribute__((always_inline)) {
-    constexpr int b = decltype(bc)::value;
-    if (u + kWaves < u1) __builtin_amdgcn_s_waitcnt(0x0078);             // vmcnt(8), lgkmcnt(0)
-    else __builtin_amdgcn_s_waitcnt(0x0070);                             // vmcnt(0), lgkmcnt(0)
-    asm volatile("" ::: "memory");
-    // S^T = K Q^T over the tile's 32 keys (one 32 x 32 block, 8 MFMAs over d)
-    f32x16 S = f32x16{};
-    if constexpr (!kExact) {
+  bool bad = false;
+  auto load_slots = [&](int u) __attribute__((always_inline)) {
+    const int pg = (u + kWaves * (lane / kPagesPerTile)) * kPagesPerTile + lane % kPagesPerTile;
+    const bool need = pg * P < g_hi;
+    int32_t s = need && pg < pt_count ? a.indices[pt_base + pg] : -1;
+    s = (s >= 0 && s < a.num_slots) ? s : -1;
+    bad |= need && s < 0;
+    return s;
+  };
+  int u = u0 + wave;                                         // tile of the current step
+  int32_t slots = load_slots(u);
+  int u_slots = u;                                           // first tile the slots are of
+
+  // every wave holds the same rows: row r16 of each 16-row block
+  int qpos[kNB];
+  bf16x8 qop[kNB][4];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) S[e] = -msub;
-    }
+  for (int nb = 0; nb < kNB; ++nb) {
+    const int rr = it.row0 + min(16 * nb + r16, rows - 1);
+    const int tok = rr / G;
+    const int head = it.kvh * G + (rr - tok * G);
+    qpos[nb] = pre + tok;
+    const uint16_t* qrow = a.q + ((int64_t)(it.q_start + tok) * a.Hq + head) * kHD;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr[i], qop[i], S, 0, 0, 0);
-    if (u + kWaves < u1) load_k(u + kWaves, kr);
-    // mask keys past the row's own position or the item's end
-    const int ts = u * kDecKeys;
-    if (ts + kDecKeys > w_full) {
-      const int lim = min(qpos, g_hi - 1);
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int key = ts + 8 * (e >> 2) + 4 * hh + (e & 3);
-        if (key > lim) S[e] = -INFINITY;
-      }
-    }
-    // offset test (exact scale: whenever the row max grows; folded: past 2^kRescaleLog2)
-    float mx = S[0];
-#pragma unroll
-    for (int e = 1; e < 16; ++e) mx = vmax(mx, S[e]);
-    mx = pair_max(mx);
-    const float cand = kExact ? mx * a.c : mx + msub;
-    if (__ballot(cand > m_used + (kExact ? kRescaleLog2Exact : kRescaleLog2))) {
-      const float m_new = fmaxf(m_used, cand);
-      const float alpha = (m_new == -INFINITY) ? 1.f : exp2f_fast(m_used - m_new);
-      m_used = m_new;
-      const float msub_new = (m_used == -INFINITY) ? 0.f : m_used;
-      const float shift = msub_new - msub;
-      msub = msub_new;
-      l *= alpha;
-#pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) oacc[dt][e] *= alpha;
+    for (int ks = 0; ks < 4; ++ks) {
+      qop[nb][ks] = ld_bf16x8(qrow + 32 * ks + 8 * g);
       if constexpr (!kExact) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) S[e] -= shift;
-      } else {
-        (void)shift;
+        for (int e = 0; e < 8; ++e) qop[nb][ks][e] = (__bf16)((float)qop[nb][ks][e] * a.c);
       }
     }
-    // P = exp2(x), packed to bf16 in the P^T operand order (16-key group g,
-    // slots 2 (j & 3) and 2 (j & 3) + 1 from accumulator 8 g + 2 (j & 3) + h)
-    bf16x8 pop[2];
+  }
+
+  auto slice = [&](int w, int b) __attribute__((always_inline)) {          // slice b of wave w
+    return (b ? (w & 2 ? v1 : v0) : (w & 2 ? k1 : k0)) + (w & 1) * kSliceBytes;
+  };
+  lds_u8* const vslice[2] = {slice(wave, 0), slice(wave, 1)};
+  const int64_t slot_bytes = (int64_t)a.Hkv * P * kHD * 2;
+  // a page's resource: nothing in it when the page is not to be read
+  auto page_rsrc = [&](const uint16_t* pool, int32_t s) __attribute__((always_inline)) {
+    return __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<void*>((const void*)((const char*)pool + (int64_t)max(s, 0) * slot_bytes)), (short)0,
+        s >= 0 ? (int)slot_bytes : 0, 0x00020000);
+  };
+  auto slot_of = [&](int t, int p) __attribute__((always_inline)) {
+    return __builtin_amdgcn_readlane(slots, (t - u_slots) / kWaves * kPagesPerTile + p);
+  };
+  // Every tile issues exactly 8 K loads and 8 V loads, so that "at most the
+  // next tile's loads may still be outstanding" is an exact wait: a row that
+  // must not be read gets an offset past its page's resource, which returns
+  // zeros -- into registers or into LDS alike.
+  constexpr uint32_t kOutside = 0x80000000u;
+  // K of tile t: [16-key block][32-d step], lane l holds key l % 16, d 8 (l / 16) on
+  auto load_k = [&](int t, bf16x8 (&kr)[2][4]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      const int key = 16 * kb + r16;
+      const __amdgpu_buffer_rsrc_t r = page_rsrc(a.k, slot_of(t, kb * kPagesPerTile / 2));
+      const uint32_t off = t * kDecKeys + key < g_hi ? (uint32_t)((it.kvh * P + key % P) * (kHD * 2) + g * 16) : kOutside;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+        kr[kb][ks] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, off + ks * 64, 0, 0));
+    }
+  };
+  // V of tile t into an LDS slice: load j fills rows 4j .. 4j + 3, lane i one
+  // 16-byte chunk of row 4j + i / 16, XOR-swizzled so that the transposed
+  // reads of 8 keys x 32 bytes touch every bank once.  Keys past the item's end
+  // and absent pages are zero rows, which keep the masked products finite.
+  auto load_v = [&](int t, lds_u8* dst) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const int g = j >> 2, e = 2 * (j & 3);
-      const float x0 = S[8 * g + e], x1 = S[8 * g + e + 1];
-      const float p0 = kExact ? exp2f_fast(__builtin_fmaf(x0, a.c, -msub)) : exp2f_fast(x0);
-      const float p1 = kExact ? exp2f_fast(__builtin_fmaf(x1, a.c, -msub)) : exp2f_fast(x1);
-      pop[g][e] = (__bf16)p0;
-      pop[g][e + 1] = (__bf16)p1;
-      l += p0 + p1;
+      const int key = 4 * j + g;
+      const __amdgpu_buffer_rsrc_t r = page_rsrc(a.v, slot_of(t, (4 * j) / P));
+      const uint32_t off = (uint32_t)((it.kvh * P + key % P) * (kHD * 2) + ((r16 ^ swz_dec(key)) << 4));
+      __attribute__((address_space(3))) void* d = (__attribute__((address_space(3))) void*)(dst + j * 1024);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, d, 16, t * kDecKeys + key < g_hi ? off : kOutside, 0, 0, 0);
     }
-    // O^T += V^T P^T: 2 groups of 16 keys x 4 blocks of 32 d
+  };
+  // the slots of tile t are at hand (wave-uniform; every 32nd or 64th tile of the wave loads the next ones)
+  auto need_slots = [&](int t) __attribute__((always_inline)) {
+    if (t - u_slots >= kWaves * kSlotTiles) {
+      u_slots = t;
+      slots = load_slots(t);
+    }
+  };
+
+  f32x4 oacc[kNB][8];                                        // [16-d block]: d 16 db + 4 g + r of row r16
+#pragma unroll
+  for (int nb = 0; nb < kNB; ++nb)
+#pragma unroll
+    for (int db = 0; db < 8; ++db) oacc[nb][db] = f32x4{};
+  float m_used[kNB], msub[kNB], l[kNB];
+#pragma unroll
+  for (int nb = 0; nb < kNB; ++nb) {
+    m_used[nb] = -INFINITY;
+    msub[nb] = 0.f;
+    l[nb] = 0.f;
+  }
+  bf16x8 kr[2][2][4];
+
+  // Issue order: K(u), V(u), K(u + 4), V(u + 4); then in the step of tile u,
+  // K(u + 8) once S(u) has read K(u) out of its registers, and V(u + 8) once the
+  // PV product has read V(u) out of its slice.  So at the top of a step at most
+  // V(u), K(u + 4) and V(u + 4) may be outstanding, and before the PV product
+  // K(u + 4), V(u + 4) and K(u + 8).  The compiler waits for the K registers by
+  // itself; the waits for V in LDS are the ones below.
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const int t = u + b * kWaves;
+    if (t < u1) {
+      load_k(t, kr[b]);
+      load_v(t, vslice[b]);
+    }
+  }
+  const int tr_key = 4 * g + (r16 >> 2), tr_d = 4 * (r16 & 3);
+  auto step = [&](auto bc) __attribute__((always_inline)) {
+    constexpr int b = decltype(bc)::value;
+    // S^T = K Q^T: two 16-key blocks
+    f32x4 S[kNB][2];
+#pragma unroll
+    for (int nb = 0; nb < kNB; ++nb)
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+        const float init = kExact ? 0.f : -msub[nb];
+        S[nb][kb] = f32x4{init, init, init, init};
+      }
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int nb = 0; nb < kNB; ++nb)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+          S[nb][kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kr[b][kb][ks], qop[nb][ks], S[nb][kb], 0, 0, 0);
+    const int t2 = u + 2 * kWaves;
+    if (t2 < u1) {
+      need_slots(t2);
+      load_k(t2, kr[b]);
+    }
+    const int ts = u * kDecKeys;
+    bf16x8 pop[kNB];
+#pragma unroll
+    for (int nb = 0; nb < kNB; ++nb) {
+      f32x4* const X = S[nb];
+      // mask keys past the row's own position or the item's end
+      if (ts + kDecKeys > w_full) {
+        const int lim = min(qpos[nb], g_hi - 1);
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (ts + 16 * kb + 4 * g + e > lim) X[kb][e] = -INFINITY;
+      }
+      // offset test (exact scale: whenever the row max grows; folded: past 2^kRescaleLog2)
+      float mx = X[0][0];
+#pragma unroll
+      for (int e = 1; e < 8; ++e) mx = vmax(mx, X[e >> 2][e & 3]);
+      mx = quad_max(mx);
+      const float cand = kExact ? mx * a.c : mx + msub[nb];
+      if (__ballot(cand > m_used[nb] + (kExact ? kRescaleLog2Exact : kRescaleLog2))) {
+        const float m_new = fmaxf(m_used[nb], cand);
+        const float alpha = (m_new == -INFINITY) ? 1.f : exp2f_fast(m_used[nb] - m_new);
+        m_used[nb] = m_new;
+        const float msub_new = (m_new == -INFINITY) ? 0.f : m_new;
+        const float shift = msub_new - msub[nb];
+        msub[nb] = msub_new;
+        l[nb] *= alpha;
+#pragma unroll
+        for (int db = 0; db < 8; ++db) oacc[nb][db] *= alpha;
+        if constexpr (!kExact) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) X[e >> 2][e & 3] -= shift;
+        } else {
+          (void)shift;
+        }
+      }
+      float ls[2] = {0.f, 0.f};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float x = X[e >> 2][e & 3];
+        const float p = kExact ? exp2f_fast(__builtin_fmaf(x, a.c, -msub[nb])) : exp2f_fast(x);
+        pop[nb][e] = (__bf16)p;
+        ls[e & 1] += p;
+      }
+      l[nb] += ls[0] + ls[1];
+    }
+    // O^T += V^T P^T: 8 blocks of 16 d, all 32 keys in one k-step
+    if (t2 < u1) __builtin_amdgcn_s_waitcnt(0x4F78);         // vmcnt(24): V(u) landed
+    else if (u + kWaves < u1) __builtin_amdgcn_s_waitcnt(0x4F70);   // vmcnt(16)
+    else __builtin_amdgcn_s_waitcnt(0x0F70);                 // vmcnt(0)
+    asm volatile("" ::: "memory");
     const lds_u8* const vb = vslice[b];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int db = 0; db < 8; ++db) {
       bf16x8 vop;
 #pragma unroll
-      for (int r = 0; r < 2; ++r) {
-        const int vkey = 16 * (i >> 2) + 8 * r + tr_key;
-        const int d = 32 * (i & 3) + tr_d;
-        const bf16x4 x = lds_read_tr(vb + vkey * 256 + ((((d >> 3) ^ swz_v(vkey)) << 4) | ((d & 7) << 1)));
+      for (int h = 0; h < 2; ++h) {
+        const int vkey = 16 * h + tr_key;
+        const int d = 16 * db + tr_d;
+        const bf16x4 x = lds_read_tr(vb + vkey * 256 + ((((d >> 3) ^ swz_dec(vkey)) << 4) | ((d & 7) << 1)));
 #pragma unroll
-        for (int e = 0; e < 4; ++e) vop[4 * r + e] = x[e];
+        for (int e = 0; e < 4; ++e) vop[4 * h + e] = x[e];
       }
-      oacc[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop, pop[i >> 2], oacc[i & 3], 0, 0, 0);
+#pragma unroll
+      for (int nb = 0; nb < kNB; ++nb)
+        oacc[nb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop, pop[nb], oacc[nb][db], 0, 0, 0);
     }
     __builtin_amdgcn_s_waitcnt(0xC07F);                    // lgkmcnt(0): V operands read out of LDS
     asm volatile("" ::: "memory");
-    if (u + 2 * kWaves < u1) load_v(u + 2 * kWaves, vslice[b]);
+    if (t2 < u1) load_v(t2, vslice[b]);
     u += kWaves;
   };
   while (u < u1) {
@@ -1112,92 +1282,153 @@ __device__ __attribute__((always_inline)) inline void decode_group(const AttnArg
     if (u >= u1) break;
     step(IntC<1>{});
   }
-  if (bad && lane == 0) atomicOr(a.err, 1);
+  if (__ballot(bad) != 0 && lane == 0) atomicOr(a.err, 1);
 
-  // ---- merge the four waves' partial results through LDS (the tile slices are free)
+  // ---- merge the four waves' partial results through LDS (their slices are
+  // free): every wave leaves the rows it has, and all 256 threads combine,
+  // thread by (row, four d), straight to the output or the part's partial
+  __attribute__((address_space(3))) float* const sm = stats;
+  __attribute__((address_space(3))) float* const sl = stats + kWaves * kDecRows;
+  __attribute__((address_space(3))) int* const flag = (__attribute__((address_space(3))) int*)(stats + 2 * kWaves * kDecRows);
+  auto piece = [&](int w, int row, int c) __attribute__((always_inline)) {   // 16-byte piece c of a row, spread over the banks
+    return (__attribute__((address_space(3))) f32x4*)((row < 16 ? slice(w, 0) : slice(w, 1)) + (row & 15) * (kHD * 4) +
+                                                     ((c ^ (row & 7)) << 4));
+  };
+#pragma unroll
+  for (int nb = 0; nb < kNB; ++nb) {
+    const int row = 16 * nb + r16;
+    const float lt = quad_sum(l[nb]);
+    if (row < rows) {
+#pragma unroll
+      for (int db = 0; db < 8; ++db) *piece(wave, row, 4 * db + g) = oacc[nb][db];
+      if (g == 0) {
+        sm[wave * kDecRows + row] = m_used[nb];
+        sl[wave * kDecRows + row] = lt;
+      }
+    }
+  }
+  __syncthreads();
+  const bool whole = it.part < 0;
+  const __amdgpu_buffer_rsrc_t rp = part_rsrc(a);
+  const uint32_t l_base = whole ? 0u : (uint32_t)a.n_parts * (kPipeRows * kHD * 4);
+  const int per = rows * (kHD / 4);                         // 16-byte pieces of the item's rows
+  for (int e = tid; e < per; e += 256) {
+    const int row = e >> 5, c = e & 31;
+    float m = sm[row];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) m = fmaxf(m, sm[w * kDecRows + row]);
+    const float sub = m == -INFINITY ? 0.f : m;
+    f32x4 o = f32x4{};
+    float lsum = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const float f = exp2f_fast(sm[w * kDecRows + row] - sub);
+      lsum += f * sl[w * kDecRows + row];
+      o += f * *piece(w, row, c);
+    }
+    const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
+    const float lse2 = lsum > 0.f ? m + __builtin_amdgcn_logf(lsum) : -INFINITY;
+    o *= inv;
+    if (whole) {
+      const int r = it.row0 + row, tok = r / G;
+      const int64_t orow = (int64_t)(it.q_start + tok) * a.Hq + it.kvh * G + (r - tok * G);
+      st_bf16x4(a.o + orow * kHD + 4 * c, o[0], o[1], o[2], o[3]);
+      if (a.lse != nullptr && c == 0) a.lse[orow] = lse2 * 0.69314718055994531f;
+    } else {
+      part_st4(rp, (uint32_t)it.part * (kPipeRows * kHD * 4) + (uint32_t)e * 16, o);
+      if (c == 0) part_st1(rp, l_base + (uint32_t)it.part * (kPipeRows * 4) + row * 4, 0, lse2);
+    }
+  }
+  if (whole) return;
+  // A key-range part: counted once all of its stores are acknowledged; the
+  // block of the last part merges the item's parts, its threads spread over
+  // (row, four d, every nsub-th part).
+  const PartInfo pi = ld_uniform(a.part_info + it.part);
+  asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(0x0070);
   __syncthreads();
-  // wave w > 0 leaves its O^T in one 16 KB array (k0, k1, v0), m and l in v1
-  auto xo = [&](int w) __attribute__((always_inline)) {
-    lds_u8* const x[3] = {L.k0, L.k1, L.v0};
-    return (__attribute__((address_space(3))) float*)x[w];
-  };
-  __attribute__((address_space(3))) float* const xml = (__attribute__((address_space(3))) float*)L.v1;
-  if (wave > 0) {
-    __attribute__((address_space(3))) float* const dst = xo(wave - 1);
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      const int dt = k >> 2, i = k & 3;
-      *(__attribute__((address_space(3))) f32x4*)(dst + (k * 64 + lane) * 4) =
-          f32x4{oacc[dt][4 * i], oacc[dt][4 * i + 1], oacc[dt][4 * i + 2], oacc[dt][4 * i + 3]};
-    }
-    xml[((wave - 1) * 2) * 64 + lane] = m_used;
-    xml[((wave - 1) * 2 + 1) * 64 + lane] = l;
+  if (wave == 0) {
+    const bool last = part_arrive(a, pi, 0);
+    if (lane == 0) *flag = last;
   }
   __syncthreads();
-  if (wave > 0) return;
-#pragma unroll
-  for (int w = 0; w < kWaves - 1; ++w) {
-    const float m_b = xml[(w * 2) * 64 + lane];
-    const float l_b = xml[(w * 2 + 1) * 64 + lane];
-    const float m_new = fmaxf(m_used, m_b);
-    const float alpha = (m_used == -INFINITY) ? 0.f : exp2f_fast(m_used - m_new);
-    const float beta = (m_b == -INFINITY) ? 0.f : exp2f_fast(m_b - m_new);
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      const int dt = k >> 2, i = k & 3;
-      const f32x4 ob = *(const __attribute__((address_space(3))) f32x4*)(xo(w) + (k * 64 + lane) * 4);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) oacc[dt][4 * i + e] = oacc[dt][4 * i + e] * alpha + ob[e] * beta;
-    }
-    l = l * alpha + l_b * beta;
-    m_used = m_new;
+  if (*flag == 0) return;
+  // every part's LSE into LDS (nsplit x rows <= kDecMergeLse words), while the
+  // first partial rows are on their way
+  __attribute__((address_space(3))) float* const ls = (__attribute__((address_space(3))) float*)k0;
+  const int nsub = max(1, 256 / per);                       // thread groups, each over every nsub-th part
+  const int sub = nsub > 1 ? tid / per : 0;
+  for (int i = tid; i < pi.nsplit * rows; i += 256) {
+    const int s = i / rows;
+    ls[i] = part_ld1(rp, l_base + (uint32_t)(pi.part0 + s) * (kPipeRows * 4) + (i - s * rows) * 4, 0);
   }
-  const float l_tot = pair_sum(l);
-  const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-  const float lse2 = l_tot > 0.f ? m_used + __builtin_amdgcn_logf(l_tot) : -INFINITY;
-  if (it.part < 0) {
-    if (r_row < rows_total) {
-      uint16_t* orow = a.o + ((int64_t)(sd.q_start + tok) * a.Hq + head) * kHD;
+  __syncthreads();
+  for (int e0 = 0; e0 < per; e0 += 256) {                   // several passes only past 8 rows (then nsub is 1)
+    const int e = e0 + tid - sub * per;
+    const bool mine = nsub > 1 ? sub < nsub : e < per;
+    const int row = mine ? e >> 5 : 0, c = e & 31;
+    float mx = -INFINITY;
+    for (int s = 0; s < pi.nsplit; ++s) mx = fmaxf(mx, ls[s * rows + row]);
+    const float msub2 = mx == -INFINITY ? 0.f : mx;
+    f32x4 num = f32x4{};
+    float den = 0.f;
+    if (mine) {
+      const uint32_t off = (uint32_t)pi.part0 * (kPipeRows * kHD * 4) + (uint32_t)e * 16;
+      constexpr int kBatch = 8;                             // partial rows in flight per thread
+      for (int s0 = sub; s0 < pi.nsplit; s0 += kBatch * nsub) {
+        f32x4 x[kBatch];
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int d = 32 * dt + 8 * i + 4 * hh;
-          st_bf16x4(orow + d, oacc[dt][4 * i] * inv, oacc[dt][4 * i + 1] * inv, oacc[dt][4 * i + 2] * inv,
-                    oacc[dt][4 * i + 3] * inv);
+        for (int k = 0; k < kBatch; ++k) {
+          const int s = s0 + k * nsub;
+          x[k] = part_ld4(rp, s < pi.nsplit ? off + (uint32_t)s * (kPipeRows * kHD * 4) : kOutside, 0);
         }
-      if (a.lse != nullptr && hh == 0)
-        a.lse[(int64_t)(sd.q_start + tok) * a.Hq + head] = lse2 * 0.69314718055994531f;
-    }
-  } else {
-    // partial of a key-range part: rows 0 .. 31 of the part's slot
-    float* po = a.part_o + ((int64_t)it.part * kPipeRows + (lane & 31)) * kHD;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int d = 32 * dt + 8 * i + 4 * hh;
-        *(f32x4*)(po + d) = f32x4{oacc[dt][4 * i] * inv, oacc[dt][4 * i + 1] * inv, oacc[dt][4 * i + 2] * inv,
-                                  oacc[dt][4 * i + 3] * inv};
+        for (int k = 0; k < kBatch; ++k) {
+          const int s = s0 + k * nsub;
+          const float w = s < pi.nsplit ? exp2f_fast(ls[s * rows + row] - msub2) : 0.f;
+          den += w;
+          num += w * x[k];
+        }
       }
-    if (hh == 0) a.part_lse[(int64_t)it.part * kPipeRows + (lane & 31)] = lse2;
+    }
+    if (nsub > 1) {                                         // one pass: the thread groups meet in LDS
+      __attribute__((address_space(3))) f32x4* const red = (__attribute__((address_space(3))) f32x4*)v0;
+      __attribute__((address_space(3))) float* const red_den = (__attribute__((address_space(3))) float*)v1;
+      if (mine) {
+        red[tid] = num;
+        red_den[tid] = den;
+      }
+      __syncthreads();
+      if (tid >= per) return;
+      for (int k = 1; k < nsub; ++k) {
+        num += red[k * per + tid];
+        den += red_den[k * per + tid];
+      }
+    }
+    if (mine) {
+      const float dinv = den > 0.f ? 1.f / den : 0.f;
+      const int r = it.row0 + row, tok = r / G;
+      const int64_t orow = (int64_t)(it.q_start + tok) * a.Hq + it.kvh * G + (r - tok * G);
+      st_bf16x4(a.o + orow * kHD + 4 * c, num[0] * dinv, num[1] * dinv, num[2] * dinv, num[3] * dinv);
+      if (a.lse != nullptr && c == 0)
+        a.lse[orow] = den > 0.f ? (mx + __builtin_amdgcn_logf(den)) * 0.69314718055994531f : -INFINITY;
+    }
   }
 }
 
 // One group of four waves per block, two blocks per CU.
 // kRead: the launch also writes the segment's new K/V rows (write_own_rows)
-// and reads the segment's keys from them, not from their pages.  A decode item
-// reads its keys through the pages: it is then the only reader of its rows, so
-// it writes them itself first and reads them back after a barrier; a later
-// key-range part of a split decode item that holds segment keys takes the
-// general path, which reads them from k_new / v_new.
+// and reads the segment's keys from them, not from their pages.  A whole decode
+// item reads its keys through the pages: it is the only reader of its rows, so
+// it writes them itself first and reads them back after a barrier; the parts of
+// a split one take the general path, which reads them from k_new / v_new.
 // kExact: the softmax scale is applied in fp32 to each score instead of to
 // the query rows in bf16 (one fma per score; no rounding of c q).
 template <int P, bool kPoolRsrc, bool kRead, bool kExact = false>
 __global__ __launch_bounds__(256, 2) void attn_pipe_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) uint8_t k_lds0[kTileBytes], k_lds1[kTileBytes];
   __shared__ __attribute__((aligned(1024))) uint8_t v_lds0[kTileBytes], v_lds1[kTileBytes];
+  __shared__ float dec_stats[2 * 4 * kDecRows + 1];
   const AttnItem it = ld_uniform(a.items + blockIdx.x);
   if (a.blk_clock != nullptr && threadIdx.x == 0) {
     uint64_t* r = a.blk_clock + 4 * (int64_t)blockIdx.x;
@@ -1211,16 +1442,18 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_kernel(AttnArgs a) {
     const SeqDesc sd{it.q_start, it.q_len, it.kv_len, 0};
     const PipeLds L{(lds_u8*)k_lds0, (lds_u8*)k_lds1, (lds_u8*)v_lds0, (lds_u8*)v_lds1,
                     nullptr, nullptr, nullptr, nullptr, nullptr};
-    const bool decode = kPoolRsrc && it.q_len * a.G <= kDecRows &&
-                        (!kRead || it.kv_begin == 0 || it.kv_end <= it.kv_len - it.q_len);
+    // the parts of a split item all take one path, since they share its partials' layout
+    const bool decode = it.q_len * a.G <= kDecRows && (!kRead || it.part < 0);
     if constexpr (kRead) {
       if (it.kv_begin == 0) {
         write_own_rows<P>(a, it);
         if (decode) __syncthreads();                         // its own rows, read back below
       }
     }
-    if (decode)
-      decode_group<P, kExact>(a, it, sd, L);
+    if (decode && it.q_len * a.G <= 16)
+      decode_group<P, kExact, 1>(a, it, (lds_u8*)k_lds0, (lds_u8*)k_lds1, (lds_u8*)v_lds0, (lds_u8*)v_lds1, (lds_f32*)dec_stats);
+    else if (decode)
+      decode_group<P, kExact, 2>(a, it, (lds_u8*)k_lds0, (lds_u8*)k_lds1, (lds_u8*)v_lds0, (lds_u8*)v_lds1, (lds_f32*)dec_stats);
     else
       pipe_group<P, kPoolRsrc, 1, 0, kRead, kExact>(a, it, sd, L);
   }

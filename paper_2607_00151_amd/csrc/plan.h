@@ -32,6 +32,10 @@ constexpr int kNumXcd = 8;        // MI355X: 8 accelerator complex dies, 32 CUs 
 // G query heads) take the kernel's decode path, which spreads the item's keys
 // over the block's four waves instead of its rows.
 constexpr int kDecodeRows = 32;
+// Parts of one split item.  A decode item's merge keeps the LSE of every part
+// and row in 16 KB of LDS: kMaxDecodeParts x kDecodeRows words.
+constexpr int kMaxItemParts = 255;
+constexpr int kMaxDecodeParts = 128;
 
 // One attention work item: a tile of packed query rows of one (sequence, KV
 // head) over a key range.
@@ -55,9 +59,15 @@ struct SeqDesc {
   int32_t pad;
 };
 
-// The key-range parts of one split work item, merged by log-sum-exp.
+// The key-range parts of one split work item, merged by log-sum-exp (by the
+// pipelined kernel itself, from the PartInfo of each part, or by merge_kernel).
 struct MergeGroup {
   int32_t seq, kvh, row0, nsplit, part0, pad;
+};
+
+// Of one key-range part: its item's first part and the number of its parts.
+struct PartInfo {
+  int32_t part0, nsplit;
 };
 
 // One surviving page of a commit splice.
@@ -385,42 +395,117 @@ inline void plan_attn_items(const sa_layout* layout, const std::vector<SeqDesc>&
         total_tiles += tiles;
       }
   }
-  // Split long items by key range when there are too few to fill the chip:
-  // always below one item per CU; below two per CU (both workgroup slots of
-  // a CU) only when items average >= 128 key tiles, where the pairing gains
-  // more than the partial-merge launch costs (measured: a CU's two blocks
-  // together run ~1.3x one alone; the merge adds ~10-15 us).  A cap on the
-  // parts (a caller's fixed scratch) coarsens the split until it fits.
+  // Split long items by key range where there are too few to fill the chip:
+  // one of a few block counts, whichever the model below says ends first.
+  // Measured on MI355X, per 64-key tile of a prefill item: 1.15 us where its
+  // block has a CU to itself, 1.6 us where two share one (a pair is 1.4x one
+  // alone; its blocks start and end 9 us slower); writing, reading and merging
+  // the partials of 128 rows costs a launch 19 us per 512 parts.
+  //
+  // A launch of at most num_cu blocks, or at most 2 num_cu, splits its items by
+  // the smallest chunk that fits, each into equal parts (a chunk with a rest, 61,
+  // 61, 61 and 8 tiles, ended with the long ones and was 8% slower on a 631-token
+  // segment over 12K keys, 138 against 128 us; a 256-token chunk over 4K keys,
+  // 320 parts 36 us and 256 parts 30 us).  With more items than CUs but not two
+  // per CU, whole items leave slots empty and equal parts of all of them (two to
+  // four) make further rounds.
   const int64_t n_work = (int64_t)work.size();
-  if (shape.max_parts != 0 &&
-      (n_work < num_cu || (n_work < 2 * num_cu && total_tiles >= 128 * n_work))) {
-    int64_t chunk = std::max<int64_t>(16, (total_tiles + 2 * num_cu - 1) / (2 * num_cu));
-    auto parts_for = [&](int64_t c) {
+  bool any_pre = false;
+  for (const Work& w : work) any_pre |= !w.decode;
+  if (shape.max_parts != 0 && n_work < 2 * num_cu) {
+    // Decode items are bound by HBM, not by the CU.  Alone in a launch they take
+    // parts down to kDecodeMin tiles (256 keys: one tile per wave and step, two
+    // steps in flight); beside prefill items a decode tile takes about 3/4 of the
+    // time of a prefill tile (1.2 us: its four waves wait on memory in turn).
+    constexpr int64_t kPrefillMin = 4, kDecodeMin = 4;
+    auto parts_of = [&](const Work& w, int64_t c) {
+      if (w.decode) c = any_pre ? c + c / 3 : c;
+      c = std::max(c, w.decode ? kDecodeMin : kPrefillMin);
+      const int64_t most = w.decode ? kMaxDecodeParts : kMaxItemParts;
+      return std::max<int64_t>(1, std::min((w.tiles + c - 1) / c, most));
+    };
+    int64_t longest = 1;
+    for (const Work& w : work) longest = std::max(longest, w.tiles);
+    // blocks and parts of a chunk size
+    auto count = [&](int64_t c, int64_t& parts) {
       int64_t n = 0;
-      for (const Work& w : work)
-        if (w.tiles > c) n += (w.tiles + c - 1) / c;
+      parts = 0;
+      for (const Work& w : work) {
+        const int64_t k = parts_of(w, c);
+        n += k;
+        parts += k > 1 ? k : 0;
+      }
       return n;
     };
-    if (shape.max_parts > 0)
-      while (parts_for(chunk) > shape.max_parts) chunk *= 2;
-    std::vector<Work> split;
-    for (const Work& w : work) {
-      if (w.tiles <= chunk) {
-        split.push_back(w);
-        continue;
+    auto fits = [&](int64_t c, int64_t slots) {
+      int64_t parts;
+      return count(c, parts) <= slots && (shape.max_parts < 0 || parts <= shape.max_parts);
+    };
+    auto smallest_chunk = [&](int64_t slots) {
+      int64_t lo = 1, hi = longest;
+      while (lo < hi) {
+        const int64_t mid = lo + (hi - lo) / 2;
+        if (fits(mid, slots)) hi = mid; else lo = mid + 1;
       }
-      const int64_t n = (w.tiles + chunk - 1) / chunk;
-      out.groups.push_back({w.it.seq, w.it.kvh, w.it.row0, (int32_t)n, out.n_parts, 0});
-      for (int64_t k = 0; k < n; ++k) {
-        Work p = w;
-        p.it.kv_begin = (int32_t)(k * chunk * kKT);
-        p.it.kv_end = (int32_t)std::min<int64_t>((k + 1) * chunk * kKT, w.it.kv_end);
-        p.it.part = out.n_parts++;
-        p.tiles = (p.it.kv_end - p.it.kv_begin + kKT - 1) / kKT;
-        split.push_back(p);
+      return lo;
+    };
+    int64_t chunk = longest;                       // whole items
+    if (n_work <= num_cu && !any_pre) {
+      // decode requests alone: a part for every CU, or two where that would leave
+      // more than a seventh of the launch's time to its longest parts (32 requests
+      // of 2K to 8K keys: 114 against 129 us; one of 73K keys: 66 against 59 us)
+      chunk = smallest_chunk(num_cu);
+      if (total_tiles * 7 < 6 * chunk * num_cu) chunk = smallest_chunk(2 * num_cu);
+    } else if (n_work <= num_cu) {
+      const int64_t c1 = smallest_chunk(num_cu), c2 = smallest_chunk(2 * num_cu);
+      int64_t p1, p2;
+      const int64_t n1 = count(c1, p1), n2 = count(c2, p2);
+      auto cost = [&](int64_t c, int64_t n, int64_t parts) {
+        int64_t most = 0;                          // tiles of the longest part
+        for (const Work& w : work) {
+          const int64_t k = parts_of(w, c), t = (w.tiles + k - 1) / k;
+          most = std::max(most, w.decode ? t - t / 4 : t);
+        }
+        return (n <= num_cu ? 115 * most : 160 * most + 900) + 1900 * parts / 512;
+      };
+      chunk = cost(c2, n2, p2) < cost(c1, n1, p1) ? c2 : c1;
+    } else if (total_tiles > 0) {
+      // k equal parts of every item: whole rounds of 2 num_cu blocks, and the last
+      // one at the rate of a block alone if no CU has two
+      const int64_t mean = (total_tiles + n_work - 1) / n_work;
+      int64_t best = -1;
+      for (int64_t k = 1; k <= 4; ++k) {
+        if (k > 1 && (mean / k < 16 || (shape.max_parts >= 0 && k * n_work > shape.max_parts))) break;
+        const int64_t n = n_work * k, full = n / (2 * num_cu), rest = n % (2 * num_cu);
+        const int64_t t = (mean + k - 1) / k + (k > 1 ? 5 : 0);    // each block's own start and end
+        const int64_t cost = 160 * t * full + (rest == 0 ? 0 : (rest <= num_cu ? 115 : 160) * t) +
+                           (k > 1 ? 1900 * n / 512 : 0);
+        if (best < 0 || cost < best) {
+          best = cost;
+          chunk = k == 1 ? longest : (longest + k - 1) / k;
+        }
       }
     }
-    work.swap(split);
+    if (chunk < longest && fits(chunk, INT32_MAX)) {
+      std::vector<Work> split;
+      for (const Work& w : work) {
+        const int64_t n = parts_of(w, chunk);
+        if (n <= 1) {
+          split.push_back(w);
+          continue;
+        }
+        out.groups.push_back({w.it.seq, w.it.kvh, w.it.row0, (int32_t)n, out.n_parts, 0});
+        for (int64_t k = 0; k < n; ++k) {
+          Work p = w;
+          p.it.kv_begin = (int32_t)(w.tiles * k / n * kKT);
+          p.it.kv_end = (int32_t)std::min<int64_t>(w.tiles * (k + 1) / n * kKT, w.it.kv_end);
+          p.it.part = out.n_parts++;
+          p.tiles = (p.it.kv_end - p.it.kv_begin + kKT - 1) / kKT;
+          split.push_back(p);
+        }
+      }
+      work.swap(split);
+    }
   }
   // Order: decode work first, then longest first, except that the row tiles of
   // one (sequence, KV head) prefill stay next to each other (ranked by the
@@ -539,6 +624,14 @@ inline void plan_attn_items(const sa_layout* layout, const std::vector<SeqDesc>&
   // first `boost` steps at raised priority, chosen so that under those rates
   // both blocks end at the same time: with S = L_old + L_new tiles and
   // D = L_old - L_new, boost = (S / (1 + r) - D / (1 - r)) / 2.
+  // In a mixed launch the prefill items run at raised priority throughout: a
+  // decode item's waves mostly wait for HBM, and being the older blocks of their
+  // CUs they would otherwise win the SIMDs' issue from the prefill item that
+  // bounds the launch (4 segments of 2048 over 16K with 64 decode rows: 2273
+  // against 2295 us).
+  if (mixed)
+    for (AttnItem& x : items)
+      if (x.kv_end > x.kv_begin && (int64_t)x.q_len * G > kDecodeRows) x.boost = (int32_t)item_tiles(x);
   if (pair && items.size() > (size_t)num_cu && items.size() <= 2 * (size_t)num_cu) {
     constexpr double kSlowShare = 0.715;
     auto tiles_of = [](const AttnItem& x) {

@@ -99,12 +99,19 @@ class PlanKey {
 enum PlanKind { kPlanAppend = 0, kPlanAssemble = 1, kPlanAttn = 2, kPlanAlias = 3, kPlanKinds = 4 };
 
 // Fixed device scratch of sa_segment_prefill_attn_noalloc: the launch's plan
-// (sequence records, work items, merge groups) in its first kNoAllocPlanBytes,
+// (sequence records, work items, part records) in its first kNoAllocPlanBytes,
 // the key-range partials of split items after it.  Every device the library
 // runs on holds one copy for the life of the process, shared by all contexts
 // on that device.
 constexpr size_t kNoAllocBytes = size_t(32) << 20;
 constexpr size_t kNoAllocPlanBytes = size_t(2) << 20;
+// The rest holds kNoAllocParts partials and, behind them, their arrival
+// counters (zero when the library is loaded; every launch leaves them zero).
+constexpr size_t kPartBytes = (size_t)sa::kPipeRows * (sa::kHD + 1) * sizeof(float);   // one key-range part
+constexpr size_t kPartCountBytes = sa::kPartCounters * sizeof(int32_t);
+constexpr int64_t kNoAllocParts = (int64_t)((kNoAllocBytes - kNoAllocPlanBytes) / (kPartBytes + kPartCountBytes));
+// Parts of one launch: bounds the counters a context owns from its creation.
+constexpr int64_t kMaxParts = 8192;
 constexpr int kMaxDevices = 64;
 
 }  // namespace
@@ -138,7 +145,7 @@ hipError_t scratch_address(int device, void** out) {
 struct sa_ctx {
   int device = 0;
   int num_cu = 256;
-  int32_t* d_err = nullptr;
+  int32_t* d_err = nullptr;          // the error flag, and behind it the arrival counters below
   struct DevPlan {
     uint8_t* dev = nullptr;
     size_t cap = 0;
@@ -175,6 +182,7 @@ struct sa_ctx {
   int ring_next = 0;
   float* part = nullptr;           // split-KV partials
   size_t part_cap = 0;             // bytes
+  int32_t* part_count = nullptr;   // arrival counters of kMaxParts parts, zero between launches (in d_err's allocation)
   bool exact_scale = true;         // sa_set_exact_scale (0: scale folded into q)
   bool fused_append = false;       // sa_set_fused_append (0, the default: append launch, then attention)
   hipEvent_t kernel_ev[2][2] = {};   // sa_set_kernel_events: [SA_TIMED_ATTN | SA_TIMED_PAGES][start, stop]
@@ -398,8 +406,10 @@ sa_status sa_create(int device, sa_ctx** out) {
   sa_ctx* c = new sa_ctx();
   c->device = device;
   c->num_cu = prop.multiProcessorCount;
-  hipError_t e = hipMalloc(&c->d_err, sizeof(int32_t));
-  if (e == hipSuccess) e = hipMemset(c->d_err, 0, sizeof(int32_t));
+  constexpr size_t kErrBytes = 256;
+  hipError_t e = hipMalloc(&c->d_err, kErrBytes + kMaxParts * kPartCountBytes);
+  if (e == hipSuccess) e = hipMemset(c->d_err, 0, kErrBytes + kMaxParts * kPartCountBytes);
+  if (e == hipSuccess) c->part_count = c->d_err + kErrBytes / sizeof(int32_t);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   for (int i = 0; e == hipSuccess && i < kRing; ++i)
     e = hipEventCreateWithFlags(&c->ring[i].ev, hipEventDisableTiming);
@@ -900,6 +910,8 @@ sa_status attn_launch(sa_ctx* ctx, const sa_layout* layout, int32_t layer, const
   }
   const int rows_item = 32 * var.qt * var.waves;
 
+  // the pipelined kernel merges a split item's parts itself, the others leave it to merge_kernel
+  const bool in_launch = var.pipe == 1;
   sa_ctx::AttnRec& rec = noalloc ? ctx->na_rec : ctx->attn_rec;
   PlanImage img;
   if (!same) {
@@ -907,8 +919,7 @@ sa_status attn_launch(sa_ctx* ctx, const sa_layout* layout, int32_t layer, const
     shape.rows_item = rows_item;
     shape.num_cu = ctx->num_cu;
     shape.pair_rounds = var.pipe != 2;      // the two-group kernel runs one block per CU
-    const size_t part_bytes = (size_t)rows_item * (sa::kHD + 1) * sizeof(float);   // one key-range part
-    if (noalloc) shape.max_parts = (int64_t)((kNoAllocBytes - kNoAllocPlanBytes) / part_bytes);
+    shape.max_parts = noalloc ? kNoAllocParts : kMaxParts;
     sa::AttnPlan plan;
     sa::plan_attn_items(layout, seqs, shape, &ctx->xcd, plan);
     rec.n_items = plan.items.size();
@@ -917,7 +928,14 @@ sa_status attn_launch(sa_ctx* ctx, const sa_layout* layout, int32_t layer, const
     rec.total_q = total_q;
     rec.o_seq = img.add(seqs.data(), seqs.size());
     rec.o_it = img.add(plan.items.data(), plan.items.size());
-    rec.o_gr = img.add(plan.groups.data(), plan.groups.size());
+    if (in_launch) {
+      std::vector<sa::PartInfo> info(plan.n_parts);
+      for (const sa::MergeGroup& g : plan.groups)
+        for (int k = 0; k < g.nsplit; ++k) info[g.part0 + k] = {g.part0, g.nsplit};
+      rec.o_gr = img.add(info.data(), info.size());
+    } else {
+      rec.o_gr = img.add(plan.groups.data(), plan.groups.size());
+    }
     rec.bytes = img.bytes.size();
   }
   const int32_t n_parts = rec.n_parts;
@@ -971,6 +989,12 @@ sa_status attn_launch(sa_ctx* ctx, const sa_layout* layout, int32_t layer, const
   a.lse = lse;
   a.part_o = n_parts > 0 ? part : nullptr;
   a.part_lse = n_parts > 0 ? part + (size_t)n_parts * rows_item * sa::kHD : nullptr;
+  if (n_parts > 0 && in_launch) {
+    a.part_info = (const sa::PartInfo*)(dev + rec.o_gr);
+    a.part_count = noalloc ? (int32_t*)(ctx->scratch + kNoAllocPlanBytes + kNoAllocParts * kPartBytes) : ctx->part_count;
+    a.part_bytes = (uint32_t)((size_t)n_parts * kPartBytes);
+    a.n_parts = n_parts;
+  }
   a.items = (const sa::AttnItem*)(dev + rec.o_it);
   a.seqs = (const sa::SeqDesc*)(dev + rec.o_seq);
   a.indptr = pages.indptr;
@@ -996,7 +1020,7 @@ sa_status attn_launch(sa_ctx* ctx, const sa_layout* layout, int32_t layer, const
   launch_attn(layout->page_size, var, pool_rsrc, exact, fused, dim3((unsigned)rec.n_items), (hipStream_t)stream,
               ctx->kernel_ev[SA_TIMED_ATTN], a);
   SA_HIP(hipGetLastError());
-  if (rec.n_groups > 0) {
+  if (rec.n_groups > 0 && !in_launch) {
     sa::MergeArgs m{};
     m.part_o = a.part_o;
     m.part_lse = a.part_lse;
