@@ -646,8 +646,8 @@ inline void plan_attn_items(const sa_layout* layout, const std::vector<SeqDesc>&
 }
 
 // Shape of a planned attention launch, for latency models: its workgroups,
-// the key-range parts of split items (a partial-merge launch follows when
-// there are any), its 64-key tiles, and its makespan in tiles when the items
+// the key-range parts of split items (which the
+// launch merges), its 64-key tiles, and its makespan in tiles when the items
 // are taken in launch order by the first of 2 x num_cu workgroup slots to
 // free (a decode item counts a quarter of its tiles: its four waves split
 // them).
