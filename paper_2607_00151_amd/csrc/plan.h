@@ -437,18 +437,16 @@ inline void plan_attn_items(const sa_layout* layout, const std::vector<SeqDesc>&
       }
       return n;
     };
-    auto fits = [&](int64_t c, int64_t slots) {
-      int64_t parts;
-      return count(c, parts) <= slots && (shape.max_parts < 0 || parts <= shape.max_parts);
-    };
-    auto smallest_chunk = [&](int64_t slots) {
-      int64_t lo = 1, hi = longest;
+    // smallest chunk from lo on whose blocks and parts are at most so many (both fall as it grows)
+    auto smallest_chunk_from = [&](int64_t lo, int64_t slots, int64_t most_parts) {
+      int64_t hi = longest, parts;
       while (lo < hi) {
         const int64_t mid = lo + (hi - lo) / 2;
-        if (fits(mid, slots)) hi = mid; else lo = mid + 1;
+        if (count(mid, parts) <= slots && parts <= most_parts) hi = mid; else lo = mid + 1;
       }
       return lo;
     };
+    auto smallest_chunk = [&](int64_t slots) { return smallest_chunk_from(1, slots, INT64_MAX); };
     int64_t chunk = longest;                       // whole items
     if (n_work <= num_cu && !any_pre) {
       // decode requests alone: a part for every CU, or two where that would leave
@@ -475,7 +473,7 @@ inline void plan_attn_items(const sa_layout* layout, const std::vector<SeqDesc>&
       const int64_t mean = (total_tiles + n_work - 1) / n_work;
       int64_t best = -1;
       for (int64_t k = 1; k <= 4; ++k) {
-        if (k > 1 && (mean / k < 16 || (shape.max_parts >= 0 && k * n_work > shape.max_parts))) break;
+        if (k > 1 && mean / k < 16) break;
         const int64_t n = n_work * k, full = n / (2 * num_cu), rest = n % (2 * num_cu);
         const int64_t t = (mean + k - 1) / k + (k > 1 ? 5 : 0);    // each block's own start and end
         const int64_t cost = 160 * t * full + (rest == 0 ? 0 : (rest <= num_cu ? 115 : 160) * t) +
@@ -486,7 +484,10 @@ inline void plan_attn_items(const sa_layout* layout, const std::vector<SeqDesc>&
         }
       }
     }
-    if (chunk < longest && fits(chunk, INT32_MAX)) {
+    // A cap on the parts (a caller's fixed scratch) has no say in the choice: a plan
+    // that fits it is the same with and without it, another is coarsened until it fits.
+    if (shape.max_parts >= 0) chunk = smallest_chunk_from(chunk, INT64_MAX, shape.max_parts);
+    if (chunk < longest) {
       std::vector<Work> split;
       for (const Work& w : work) {
         const int64_t n = parts_of(w, chunk);

@@ -10,6 +10,7 @@
 //     exactly once, as one whole item or as key-range parts that tile
 //     [0, kv_end) in order, with the causal key bound of the tile's last row;
 //   * split parts are numbered once each and their merge groups agree;
+//   * a cap on the parts leaves a plan that fits it as it is;
 //   * the XCD weighting moves items, never changes them, and a repeated
 //     launch reuses the same placement;
 //   * the splice plan matches a direct page-by-page count (kept tokens,
@@ -180,6 +181,38 @@ static void check_attention_case(std::mt19937_64& r, int case_id) {
               (plan.items.empty() ||
                std::memcmp(again.items.data(), plan.items.data(), plan.items.size() * sizeof(sa::AttnItem)) == 0),
           "a repeated launch changed its placement");
+  }
+}
+
+// Launches of up to 511 items and beyond, contexts to 130K keys: decode requests, short
+// segments, chunks, mixed.  A cap on the parts only ever coarsens a plan that
+// exceeds it: a plan that fits is the same with and without it (the
+// allocation-free call then gives the bits of the ordinary one).
+static void check_part_cap(std::mt19937_64& r, int case_id) {
+  const int Hkv = 1 << (r() % 4), G = std::vector<int>{1, 4, 8}[r() % 3];
+  const sa_layout L = layout(Hkv * G, Hkv, 16);
+  const int B = 1 + (int)(r() % 64), kind = (int)(r() % 4), top = 1 << (8 + r() % 10);
+  std::vector<int32_t> ql(B), kl(B);
+  for (int b = 0; b < B; ++b) {
+    ql[b] = kind == 0 ? 1 : kind == 1 ? (int)(16 + r() % 48) : kind == 2 ? (int)(1 + r() % 700) : (r() % 3 ? 1 : 256);
+    kl[b] = ql[b] + (int)(r() % (r() % 8 == 0 ? top : std::max(1, top / 8)));
+  }
+  std::string err;
+  std::vector<sa::SeqDesc> seqs;
+  int64_t total_q = 0;
+  CHECK(sa::plan_attn_check(&L, 0, B, ql.data(), kl.data(), 0.0884f, seqs, total_q, err) == SA_OK, "%s", err.c_str());
+  sa::AttnShape shape;
+  sa::AttnPlan free_plan, capped;
+  sa::plan_attn_items(&L, seqs, shape, nullptr, free_plan);
+  for (int64_t cap : {(int64_t)8192, (int64_t)476, (int64_t)(1 + r() % 300)}) {
+    shape.max_parts = cap;
+    sa::plan_attn_items(&L, seqs, shape, nullptr, capped);
+    CHECK(capped.n_parts <= cap, "case %d: %d parts over the cap %lld", case_id, capped.n_parts, (long long)cap);
+    if (free_plan.n_parts <= cap)
+      CHECK(capped.items.size() == free_plan.items.size() &&
+                std::memcmp(capped.items.data(), free_plan.items.data(), capped.items.size() * sizeof(sa::AttnItem)) == 0,
+            "case %d: %d parts fit the cap %lld, yet it changes the plan (%d parts)", case_id, free_plan.n_parts,
+            (long long)cap, capped.n_parts);
   }
 }
 
@@ -402,6 +435,7 @@ static void check_debug_checks() {
 int main() {
   std::mt19937_64 r(20260);
   for (int c = 0; c < 3000; ++c) check_attention_case(r, c);
+  for (int c = 0; c < 2000; ++c) check_part_cap(r, c);
   check_attention_errors();
   for (int c = 0; c < 3000; ++c) check_splice_case(r, c);
   check_splice_errors();
