@@ -407,8 +407,7 @@ inline void plan_attn_items(const sa_layout* layout, const std::vector<SeqDesc>&
   // 61, 61 and 8 tiles, ended with the long ones and was 8% slower on a 631-token
   // segment over 12K keys, 138 against 128 us; a 256-token chunk over 4K keys,
   // 320 parts 36 us and 256 parts 30 us).  With more items than CUs but not two
-  // per CU, whole items leave slots empty and equal parts of all of them (two to
-  // four) make further rounds.
+  // per CU, whole items leave slots empty: the last branch.
   const int64_t n_work = (int64_t)work.size();
   bool any_pre = false;
   for (const Work& w : work) any_pre |= !w.decode;
@@ -418,22 +417,34 @@ inline void plan_attn_items(const sa_layout* layout, const std::vector<SeqDesc>&
     // steps in flight); beside prefill items a decode tile takes about 3/4 of the
     // time of a prefill tile (1.2 us: its four waves wait on memory in turn).
     constexpr int64_t kPrefillMin = 4, kDecodeMin = 4;
-    auto parts_of = [&](const Work& w, int64_t c) {
-      if (w.decode) c = any_pre ? c + c / 3 : c;
-      c = std::max(c, w.decode ? kDecodeMin : kPrefillMin);
-      const int64_t most = w.decode ? kMaxDecodeParts : kMaxItemParts;
-      return std::max<int64_t>(1, std::min((w.tiles + c - 1) / c, most));
+    auto parts_of = [&](int64_t tiles, bool decode, int64_t c) {
+      if (decode) c = any_pre ? c + c / 3 : c;
+      c = std::max(c, decode ? kDecodeMin : kPrefillMin);
+      const int64_t most = decode ? kMaxDecodeParts : kMaxItemParts;
+      return std::max<int64_t>(1, std::min((tiles + c - 1) / c, most));
     };
-    int64_t longest = 1;
-    for (const Work& w : work) longest = std::max(longest, w.tiles);
+    struct RowTile {
+      int64_t tiles;
+      bool decode;
+    };
+    std::vector<RowTile> rows;                     // of one KV head: the others are alike
+    int64_t longest = 1, streamed = 0;             // streamed: tiles read at least once
+    for (size_t i = 0; i < work.size(); ++i) {
+      const Work& w = work[i];
+      if (w.it.kvh != 0) continue;
+      rows.push_back({w.tiles, w.decode});
+      longest = std::max(longest, w.tiles);
+      if (i + 1 == work.size() || work[i + 1].it.seq != w.it.seq || work[i + 1].it.kvh != 0)
+        streamed += w.tiles * Hkv;                 // the sequence's last row tile sees the most keys
+    }
     // blocks and parts of a chunk size
     auto count = [&](int64_t c, int64_t& parts) {
       int64_t n = 0;
       parts = 0;
-      for (const Work& w : work) {
-        const int64_t k = parts_of(w, c);
-        n += k;
-        parts += k > 1 ? k : 0;
+      for (const RowTile& w : rows) {
+        const int64_t k = parts_of(w.tiles, w.decode, c);
+        n += k * Hkv;
+        parts += k > 1 ? k * Hkv : 0;
       }
       return n;
     };
@@ -461,28 +472,85 @@ inline void plan_attn_items(const sa_layout* layout, const std::vector<SeqDesc>&
       auto cost = [&](int64_t c, int64_t n, int64_t parts) {
         int64_t most = 0;                          // tiles of the longest part
         for (const Work& w : work) {
-          const int64_t k = parts_of(w, c), t = (w.tiles + k - 1) / k;
+          const int64_t k = parts_of(w.tiles, w.decode, c), t = (w.tiles + k - 1) / k;
           most = std::max(most, w.decode ? t - t / 4 : t);
         }
         return (n <= num_cu ? 115 * most : 160 * most + 900) + 1900 * parts / 512;
       };
       chunk = cost(c2, n2, p2) < cost(c1, n1, p1) ? c2 : c1;
-    } else if (total_tiles > 0) {
-      // k equal parts of every item: whole rounds of 2 num_cu blocks, and the last
-      // one at the rate of a block alone if no CU has two
-      const int64_t mean = (total_tiles + n_work - 1) / n_work;
-      int64_t best = -1;
-      for (int64_t k = 1; k <= 4; ++k) {
-        if (k > 1 && mean / k < 16) break;
-        const int64_t n = n_work * k, full = n / (2 * num_cu), rest = n % (2 * num_cu);
-        const int64_t t = (mean + k - 1) / k + (k > 1 ? 5 : 0);    // each block's own start and end
-        const int64_t cost = 160 * t * full + (rest == 0 ? 0 : (rest <= num_cu ? 115 : 160) * t) +
-                           (k > 1 ? 1900 * n / 512 : 0);
-        if (best < 0 || cost < best) {
-          best = cost;
-          chunk = k == 1 ? longest : (longest + k - 1) / k;
+    } else {
+      // Whole items, the smallest chunk that fits two blocks per CU (one long
+      // context among many short ones: its parts fill the slots the others leave),
+      // chunks of one to two even shares of the slots (the same where it leaves few),
+      // or two to four parts of the longest item and the same chunk for the others
+      // (further rounds, whose blocks even out), whichever ends first by its
+      // longest parts, its pairs and the keys it streams.  Of the time bound by the
+      // pairs and that of the stream a quarter of the shorter does not overlap.  In
+      // units of 10 ns, measured (MI355X): a prefill tile 115 alone on its CU, 160 for
+      // a tile of each of two blocks; a decode tile 80 and 210; the stream 61 per
+      // tile and 100 blocks beside prefill items, 54.6 for decode items alone
+      // (5.4 and 6.0 TB/s).  Kernel times, us, of whole items, the smallest chunk, one
+      // even share, four parts of the longest: 40 decode requests, one of 128K keys and
+      // 39 of 8K: 1638, 306, 325, 555; 34 of 16K: 529, as whole, 443, 403; 40 segments
+      // of 32 tokens on those 40 contexts: 2077, 334, 357, 632; 34 over 16K: 436, as
+      // whole, 500, 466; 32 decode requests of 4K beside a 256-token chunk over 128K:
+      // 1895, 605, 590, 605.
+      const int64_t alone = any_pre ? 115 : 80, both = any_pre ? 160 : 210, slots = 2 * num_cu;
+      const int64_t stream = any_pre ? streamed * 61 / 100 : streamed * 546 / 1000;
+      struct Run {
+        int64_t tiles, blocks;
+      };
+      std::vector<Run> runs;                       // blocks of one length, longest first
+      auto cost = [&](int64_t c) {
+        runs.clear();
+        int64_t n = 0, sum = 0, parts = 0, prefill_parts = 0;
+        for (const RowTile& w : rows) {
+          const int64_t k = parts_of(w.tiles, w.decode, c);
+          int64_t t = (w.tiles + k - 1) / k;
+          if (w.decode && any_pre) t -= t / 4;
+          runs.push_back({t, k * Hkv});
+          n += k * Hkv;
+          sum += t * k * Hkv;
+          if (k > 1) parts += k * Hkv;
+          if (k > 1 && !w.decode) prefill_parts += k * Hkv;
         }
-      }
+        std::sort(runs.begin(), runs.end(), [](const Run& x, const Run& y) { return x.tiles > y.tiles; });
+        int64_t busy = 0;                          // the most loaded CU
+        if (n <= slots) {
+          // the longest n - num_cu blocks each with one of the shortest, the others alone
+          size_t i = 0, j = runs.size() - 1;
+          int64_t left_i = runs[0].blocks, left_j = runs[j].blocks, pairs = n - num_cu;
+          while (pairs > 0) {
+            busy = std::max(busy, both * runs[j].tiles + alone * (runs[i].tiles - runs[j].tiles));
+            const int64_t step = i == j ? pairs : std::min(pairs, std::min(left_i, left_j));
+            pairs -= step;
+            if ((left_i -= step) <= 0 && i < j) left_i = runs[++i].blocks;
+            if ((left_j -= step) <= 0 && j > i) left_j = runs[--j].blocks;
+          }
+          busy = std::max(busy, alone * runs[i].tiles);
+        } else {
+          const int64_t t = (sum + n - 1) / n + (any_pre ? 5 : 0);   // each block's own start and end
+          const int64_t rest = n % slots;
+          busy = n / slots * t * std::max(both, any_pre ? 0 : slots * 546 / 1000);
+          if (rest > 0)
+            busy += t * std::max(rest <= num_cu ? alone : both, any_pre ? 0 : rest * 546 / 1000);
+          busy = std::max(busy, alone * runs[0].tiles);
+        }
+        return std::max(busy, stream) + std::min(busy, stream) / 4 + 1900 * prefill_parts / 512 + (parts > 0 ? 500 : 0);
+      };
+      const int64_t mean = (total_tiles + n_work - 1) / n_work;
+      int64_t best = cost(longest);
+      auto consider = [&](int64_t c) {
+        const int64_t t = c < longest ? cost(c) : best;
+        if (t < best) {
+          best = t;
+          chunk = c;
+        }
+      };
+      consider(smallest_chunk(slots));
+      const int64_t even = std::max<int64_t>(kPrefillMin, (total_tiles + slots - 1) / slots);
+      for (int64_t c : {even, even * 3 / 2, even * 2}) consider(c);
+      for (int64_t k = 2; k <= 4 && mean / k >= 16; ++k) consider((longest + k - 1) / k);
     }
     // A cap on the parts (a caller's fixed scratch) has no say in the choice: a plan
     // that fits it is the same with and without it, another is coarsened until it fits.
@@ -490,7 +558,7 @@ inline void plan_attn_items(const sa_layout* layout, const std::vector<SeqDesc>&
     if (chunk < longest) {
       std::vector<Work> split;
       for (const Work& w : work) {
-        const int64_t n = parts_of(w, chunk);
+        const int64_t n = parts_of(w.tiles, w.decode, chunk);
         if (n <= 1) {
           split.push_back(w);
           continue;

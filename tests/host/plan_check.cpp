@@ -11,6 +11,7 @@
 //     [0, kv_end) in order, with the causal key bound of the tile's last row;
 //   * split parts are numbered once each and their merge groups agree;
 //   * a cap on the parts leaves a plan that fits it as it is;
+//   * one long context among many short ones is not left to few blocks;
 //   * the XCD weighting moves items, never changes them, and a repeated
 //     launch reuses the same placement;
 //   * the splice plan matches a direct page-by-page count (kept tokens,
@@ -214,6 +215,38 @@ static void check_part_cap(std::mt19937_64& r, int case_id) {
             "case %d: %d parts fit the cap %lld, yet it changes the plan (%d parts)", case_id, free_plan.n_parts,
             (long long)cap, capped.n_parts);
   }
+}
+
+// Launches of more items than CUs but not two per CU, a few long contexts among
+// short ones (decode requests, short segments or both): no block is left with
+// far more than an even share of the 512 slots.  Equal items stay whole at up to
+// twice the share; a decode block alone on its CU runs 3.5 shares while the launch
+// streams (0.8 us a tile, 2.8 us for a tile of every slot).
+static void check_ragged_balance(std::mt19937_64& r, int case_id) {
+  const int Hkv = 8, G = 4;
+  const sa_layout L = layout(Hkv * G, Hkv, 16);
+  const int B = 33 + (int)(r() % 31), kind = (int)(r() % 3), n_long = 1 + (int)(r() % 5);
+  const int shrt = 1 << (10 + r() % 4), lng = shrt << (1 + r() % 7);
+  std::vector<int32_t> ql(B), kl(B);
+  for (int b = 0; b < B; ++b) {
+    ql[b] = kind == 0 ? 1 : kind == 1 ? 32 : (r() % 2 ? 1 : 32);
+    kl[b] = b < n_long ? lng : shrt + (int)(r() % shrt);
+  }
+  std::string err;
+  std::vector<sa::SeqDesc> seqs;
+  int64_t total_q = 0, tiles = 0, longest = 0;
+  CHECK(sa::plan_attn_check(&L, 0, B, ql.data(), kl.data(), 0.0884f, seqs, total_q, err) == SA_OK, "%s", err.c_str());
+  sa::AttnShape shape;
+  sa::AttnPlan plan;
+  sa::plan_attn_items(&L, seqs, shape, nullptr, plan);
+  for (const sa::AttnItem& it : plan.items) {
+    if (it.kv_end <= it.kv_begin) continue;
+    tiles += sa::item_tiles(it);
+    longest = std::max(longest, sa::item_tiles(it));
+  }
+  const int64_t even = (tiles + 511) / 512;
+  CHECK(longest <= 4 * even, "case %d: %d sequences, kind %d, %d of %d keys: longest block %lld tiles, even share %lld",
+        case_id, B, kind, n_long, lng, (long long)longest, (long long)even);
 }
 
 static void check_attention_errors() {
@@ -436,6 +469,7 @@ int main() {
   std::mt19937_64 r(20260);
   for (int c = 0; c < 3000; ++c) check_attention_case(r, c);
   for (int c = 0; c < 2000; ++c) check_part_cap(r, c);
+  for (int c = 0; c < 1000; ++c) check_ragged_balance(r, c);
   check_attention_errors();
   for (int c = 0; c < 3000; ++c) check_splice_case(r, c);
   check_splice_errors();
