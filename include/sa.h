@@ -49,7 +49,11 @@
  *   - A context keeps per-call plans (work lists) in device memory and reuses
  *     an uploaded plan when the next call of the same kind needs the same one.
  *     Calls on one context must therefore be ordered: use one stream per
- *     context (or one context per stream / thread).
+ *     context (or one context per stream / thread).  Attention calls that
+ *     overlap all the same may also leave the counters by which a launch split
+ *     by key range merges its parts off, and then later split launches of the
+ *     context give wrong outputs until sa_sync_check has reported and cleared
+ *     them.
  *   - Page ids inside device tables are range-checked by the kernels: a page
  *     beyond a sequence's list or a slot outside [0, num_slots) is skipped
  *     (never dereferenced) and latched in a device flag that sa_sync_check
@@ -85,7 +89,8 @@ typedef enum sa_status {
     SA_ERR_NO_PAGES = 6,      /* free list or destination table too small               */
     SA_ERR_HIP = 7,           /* a HIP runtime call failed (see sa_last_error)          */
     SA_ERR_DEVICE = 8,        /* no usable gfx950 device                                 */
-    SA_ERR_OVERLAP = 9        /* slot lists repeat where they must not (SA_DEBUG checks) */
+    SA_ERR_OVERLAP = 9        /* slot lists repeat where they must not (SA_DEBUG checks),
+                                 or split launches overlapped (sa_sync_check)           */
 } sa_status;
 
 typedef struct sa_ctx sa_ctx;
@@ -152,7 +157,11 @@ sa_status sa_attn_plan_stats(const sa_layout *layout, int32_t batch, const int32
                              const int32_t *h_kv_len, int32_t num_cu, int64_t *out);
 
 /* Wait for `stream`, then report SA_ERR_RANGE if any kernel of this context
- * met an out-of-range page id or slot since the last check (and clear it). */
+ * met an out-of-range page id or slot since the last check (and clear it), or
+ * SA_ERR_OVERLAP if launches split by key range overlapped against the rules
+ * above and left the context's arrival counters off (and clear them; only then,
+ * or while a launch of the context still runs on another stream, it also waits
+ * for the device). */
 sa_status sa_sync_check(sa_ctx *ctx, void *stream);
 
 /*
@@ -311,12 +320,14 @@ sa_status sa_segment_prefill_attn(sa_ctx *ctx, const sa_layout *layout, int32_t 
  * allocated at sa_create.  Limits: the plan (about 40 bytes per work item, a
  * work item per sequence, KV head and 128 packed query rows) must fit 2 MiB,
  * else SA_ERR_SHAPE before anything is enqueued; the partials get the other
- * 30 MiB (476 key-range parts of 128 rows and their counters), and a launch
- * that would split into more parts is split more coarsely instead.  Every call on one GPU uses
+ * 30 MiB (476 key-range parts of 128 rows), and a launch that would split
+ * into more parts is split more coarsely instead.  Every call on one GPU uses
  * that GPU's array, whichever context makes it, and leaves the last call's
  * contents there: calls that overlap in time on one GPU (two streams, two
- * contexts) race, so order them.  The call may wait on the host for the
- * previous plan copy of the same context to finish.
+ * contexts) race, so order them; their outputs are undefined, and those of the
+ * same contexts' later split launches until sa_sync_check (see there).  The
+ * call may wait on the host for the previous plan copy of the same context to
+ * finish.
  * Errors: those of sa_segment_prefill_attn.
  */
 sa_status sa_segment_prefill_attn_noalloc(sa_ctx *ctx, const sa_layout *layout, int32_t layer,

@@ -102,16 +102,22 @@ enum PlanKind { kPlanAppend = 0, kPlanAssemble = 1, kPlanAttn = 2, kPlanAlias = 
 // (sequence records, work items, part records) in its first kNoAllocPlanBytes,
 // the key-range partials of split items after it.  Every device the library
 // runs on holds one copy for the life of the process, shared by all contexts
-// on that device.
+// on that device.  The arrival counters are the calling context's: calls of two
+// contexts that overlap spoil each other's plan and partials, which every call
+// writes again, but would leave counters off for good.  (Clearing counters in
+// the scratch with every call's plan copy instead: packed into a few lines they
+// cost a 256-token chunk over 4K keys 1 us of contended arrivals, 36.5 against
+// 35.4 us; unpacked the copy passes 16 KB, where the runtime takes 16 us more.)
 constexpr size_t kNoAllocBytes = size_t(32) << 20;
 constexpr size_t kNoAllocPlanBytes = size_t(2) << 20;
-// The rest holds kNoAllocParts partials and, behind them, their arrival
-// counters (zero when the library is loaded; every launch leaves them zero).
+// The rest holds kNoAllocParts partials (476).
 constexpr size_t kPartBytes = (size_t)sa::kPipeRows * (sa::kHD + 1) * sizeof(float);   // one key-range part
 constexpr size_t kPartCountBytes = sa::kPartCounters * sizeof(int32_t);
-constexpr int64_t kNoAllocParts = (int64_t)((kNoAllocBytes - kNoAllocPlanBytes) / (kPartBytes + kPartCountBytes));
+constexpr int64_t kNoAllocParts = (int64_t)((kNoAllocBytes - kNoAllocPlanBytes) / kPartBytes);
 // Parts of one launch: bounds the counters a context owns from its creation.
 constexpr int64_t kMaxParts = 8192;
+static_assert(kNoAllocParts <= kMaxParts, "the allocation-free call counts in the context's counters");
+constexpr size_t kErrBytes = 256;              // the error flag, padded
 constexpr int kMaxDevices = 64;
 
 }  // namespace
@@ -182,6 +188,7 @@ struct sa_ctx {
   int ring_next = 0;
   float* part = nullptr;           // split-KV partials
   size_t part_cap = 0;             // bytes
+  int64_t parts_used = 0;          // most parts any launch has had
   int32_t* part_count = nullptr;   // arrival counters of kMaxParts parts, zero between launches (in d_err's allocation)
   bool exact_scale = true;         // sa_set_exact_scale (0: scale folded into q)
   bool fused_append = false;       // sa_set_fused_append (0, the default: append launch, then attention)
@@ -406,7 +413,6 @@ sa_status sa_create(int device, sa_ctx** out) {
   sa_ctx* c = new sa_ctx();
   c->device = device;
   c->num_cu = prop.multiProcessorCount;
-  constexpr size_t kErrBytes = 256;
   hipError_t e = hipMalloc(&c->d_err, kErrBytes + kMaxParts * kPartCountBytes);
   if (e == hipSuccess) e = hipMemset(c->d_err, 0, kErrBytes + kMaxParts * kPartCountBytes);
   if (e == hipSuccess) c->part_count = c->d_err + kErrBytes / sizeof(int32_t);
@@ -483,12 +489,30 @@ sa_status sa_sync_check(sa_ctx* ctx, void* stream) {
   sa_status s = check_ctx(ctx);
   if (s != SA_OK) return s;
   SA_HIP(hipStreamSynchronize((hipStream_t)stream));
-  int32_t flag = 0;
-  SA_HIP(hipMemcpy(&flag, ctx->d_err, sizeof flag, hipMemcpyDeviceToHost));
-  if (flag) {
-    SA_HIP(hipMemset(ctx->d_err, 0, sizeof(int32_t)));
-    return fail(SA_ERR_RANGE, "a kernel met an out-of-range page id or slot (flags 0x%x)", flag);
+  // the flag and, behind it, the arrival counters of every part used so far
+  std::vector<int32_t> w((kErrBytes + ctx->parts_used * kPartCountBytes) / sizeof(int32_t));
+  auto fetch = [&] { return hipMemcpy(w.data(), ctx->d_err, w.size() * sizeof(int32_t), hipMemcpyDeviceToHost); };
+  auto counting = [&] {
+    return std::any_of(w.begin() + kErrBytes / sizeof(int32_t), w.end(), [](int32_t c) { return c != 0; });
+  };
+  SA_HIP(fetch());
+  bool off = false;
+  if (counting()) {
+    // a launch ordered behind `stream` may still count; once nothing runs they are zero or off
+    SA_HIP(hipDeviceSynchronize());
+    SA_HIP(fetch());
+    off = counting();
+    if (off) {
+      SA_HIP(hipMemset(ctx->part_count, 0, ctx->parts_used * kPartCountBytes));
+      SA_HIP(hipDeviceSynchronize());
+    }
   }
+  if (w[0]) SA_HIP(hipMemset(ctx->d_err, 0, sizeof(int32_t)));
+  if (off)
+    return fail(SA_ERR_OVERLAP, "launches split by key range overlapped on this context (or in the allocation-free "
+                "call's scratch): outputs since the last check may be wrong; its arrival counters are cleared%s",
+                w[0] ? "; a kernel also met an out-of-range page id or slot" : "");
+  if (w[0]) return fail(SA_ERR_RANGE, "a kernel met an out-of-range page id or slot (flags 0x%x)", w[0]);
   return SA_OK;
 }
 
@@ -991,7 +1015,8 @@ sa_status attn_launch(sa_ctx* ctx, const sa_layout* layout, int32_t layer, const
   a.part_lse = n_parts > 0 ? part + (size_t)n_parts * rows_item * sa::kHD : nullptr;
   if (n_parts > 0 && in_launch) {
     a.part_info = (const sa::PartInfo*)(dev + rec.o_gr);
-    a.part_count = noalloc ? (int32_t*)(ctx->scratch + kNoAllocPlanBytes + kNoAllocParts * kPartBytes) : ctx->part_count;
+    a.part_count = ctx->part_count;
+    ctx->parts_used = std::max<int64_t>(ctx->parts_used, n_parts);
     a.part_bytes = (uint32_t)((size_t)n_parts * kPartBytes);
     a.n_parts = n_parts;
   }

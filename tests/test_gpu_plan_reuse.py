@@ -87,6 +87,32 @@ def test_bad_lengths_are_refused_after_a_kept_plan():
         assert e.value.name == "SA_ERR_NULL"
 
 
+@pytest.mark.parametrize("entry", ["sa_segment_prefill_attn", "sa_segment_prefill_attn_noalloc"])
+def test_arrival_counters_left_off_are_reported_and_cleared(entry):
+    """Counters that overlapping launches would leave off (set here from the host, between
+    launches): sa_sync_check reports and clears them, and the next split launch is whole again."""
+    fn = getattr(sa, entry)
+    w = CASES["split"]()
+    cache = build_cache(w)
+    hip = sa.load_library()                                  # its HIP runtime's entry points too
+    hip.hipMemcpy.restype = sa.ctypes.c_int
+    with sa.Context(0) as ctx:
+        want = attend(fn, ctx, w, cache)
+        sa.sa_sync_check(ctx)
+        head = (sa.ctypes.c_int32 * 2).from_address(ctx.handle.value)   # {device, compute units}, then the flag's address
+        assert list(head) == [0, torch.cuda.get_device_properties(0).multi_processor_count]
+        flag = sa.ctypes.c_uint64.from_address(ctx.handle.value + 8).value
+        one = np.ones(1, dtype=np.int32)
+        assert hip.hipMemcpy(sa.ctypes.c_void_p(flag + 256), sa.ctypes.c_void_p(one.ctypes.data), sa.ctypes.c_size_t(4), 1) == 0
+        with pytest.raises(sa.SaError) as e:
+            sa.sa_sync_check(ctx)
+        assert e.value.name == "SA_ERR_OVERLAP"
+        sa.sa_sync_check(ctx)
+        o, lse = attend(fn, ctx, w, cache)
+        assert torch.equal(o, want[0]) and torch.equal(lse, want[1])
+        sa.sa_sync_check(ctx)
+
+
 @pytest.mark.parametrize("mode", ["copy", "alias"])
 def test_splice_and_append_plans_reused_and_replaced(mode):
     """Two batches of one shape but other spans, kept lengths and capacities, in turn on one context."""
