@@ -1353,8 +1353,8 @@ __device__ __attribute__((always_inline)) inline void decode_group(const AttnArg
   }
   __syncthreads();
   if (*flag == 0) return;
-  // every part's LSE into LDS (nsplit x rows <= kDecMergeLse words), while the
-  // first partial rows are on their way
+  // every part's LSE into LDS: nsplit x rows words, in the room of one K tile
+  static_assert(kMaxDecodeParts * kDecRows * sizeof(float) <= kTileBytes, "the LSEs of an item's parts fit k0");
   __attribute__((address_space(3))) float* const ls = (__attribute__((address_space(3))) float*)k0;
   const int nsub = max(1, 256 / per);                       // thread groups, each over every nsub-th part
   const int sub = nsub > 1 ? tid / per : 0;

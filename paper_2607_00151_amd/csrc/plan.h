@@ -32,8 +32,8 @@ constexpr int kNumXcd = 8;        // MI355X: 8 accelerator complex dies, 32 CUs 
 // G query heads) take the kernel's decode path, which spreads the item's keys
 // over the block's four waves instead of its rows.
 constexpr int kDecodeRows = 32;
-// Parts of one split item.  A decode item's merge keeps the LSE of every part
-// and row in 16 KB of LDS: kMaxDecodeParts x kDecodeRows words.
+// Most parts of one split item.  A decode item's merge keeps the LSE of every
+// part and row in 16 KB of LDS: kMaxDecodeParts x kDecodeRows words.
 constexpr int kMaxItemParts = 255;
 constexpr int kMaxDecodeParts = 128;
 

@@ -10,6 +10,7 @@
 //     exactly once, as one whole item or as key-range parts that tile
 //     [0, kv_end) in order, with the causal key bound of the tile's last row;
 //   * split parts are numbered once each and their merge groups agree;
+//   * no item has more parts than its merge has room for, limits reached;
 //   * a cap on the parts leaves a plan that fits it as it is;
 //   * one long context among many short ones is not left to few blocks;
 //   * the XCD weighting moves items, never changes them, and a repeated
@@ -189,14 +190,15 @@ static void check_attention_case(std::mt19937_64& r, int case_id) {
 // segments, chunks, mixed.  A cap on the parts only ever coarsens a plan that
 // exceeds it: a plan that fits is the same with and without it (the
 // allocation-free call then gives the bits of the ordinary one).
+static int g_most_parts[2];                    // of a prefill and of a decode item
 static void check_part_cap(std::mt19937_64& r, int case_id) {
   const int Hkv = 1 << (r() % 4), G = std::vector<int>{1, 4, 8}[r() % 3];
   const sa_layout L = layout(Hkv * G, Hkv, 16);
-  const int B = 1 + (int)(r() % 64), kind = (int)(r() % 4), top = 1 << (8 + r() % 10);
+  const int B = r() % 8 == 0 ? 1 : 1 + (int)(r() % 64), kind = (int)(r() % 4), top = 1 << (8 + r() % 10);
   std::vector<int32_t> ql(B), kl(B);
   for (int b = 0; b < B; ++b) {
     ql[b] = kind == 0 ? 1 : kind == 1 ? (int)(16 + r() % 48) : kind == 2 ? (int)(1 + r() % 700) : (r() % 3 ? 1 : 256);
-    kl[b] = ql[b] + (int)(r() % (r() % 8 == 0 ? top : std::max(1, top / 8)));
+    kl[b] = ql[b] + (int)(r() % (B == 1 ? 1 << 17 : r() % 8 == 0 ? top : std::max(1, top / 8)));
   }
   std::string err;
   std::vector<sa::SeqDesc> seqs;
@@ -205,6 +207,13 @@ static void check_part_cap(std::mt19937_64& r, int case_id) {
   sa::AttnShape shape;
   sa::AttnPlan free_plan, capped;
   sa::plan_attn_items(&L, seqs, shape, nullptr, free_plan);
+  // the parts of one item: a decode item's merge has LDS for kMaxDecodeParts
+  for (const sa::MergeGroup& g : free_plan.groups) {
+    const bool decode = ql[g.seq] * G <= sa::kDecodeRows;
+    CHECK(g.nsplit <= (decode ? sa::kMaxDecodeParts : sa::kMaxItemParts), "case %d: %d parts of one %s item", case_id,
+          g.nsplit, decode ? "decode" : "prefill");
+    g_most_parts[decode] = std::max(g_most_parts[decode], g.nsplit);
+  }
   for (int64_t cap : {(int64_t)8192, (int64_t)476, (int64_t)(1 + r() % 300)}) {
     shape.max_parts = cap;
     sa::plan_attn_items(&L, seqs, shape, nullptr, capped);
@@ -469,6 +478,8 @@ int main() {
   std::mt19937_64 r(20260);
   for (int c = 0; c < 3000; ++c) check_attention_case(r, c);
   for (int c = 0; c < 2000; ++c) check_part_cap(r, c);
+  CHECK(g_most_parts[1] == sa::kMaxDecodeParts && g_most_parts[0] == sa::kMaxItemParts,
+        "the draws reach %d parts of a decode item, %d of a prefill item", g_most_parts[1], g_most_parts[0]);
   for (int c = 0; c < 1000; ++c) check_ragged_balance(r, c);
   check_attention_errors();
   for (int c = 0; c < 3000; ++c) check_splice_case(r, c);
