@@ -167,8 +167,8 @@ _I32 = np.dtype(np.int32)
 
 
 def _host_i32(x):
-    # an int32 array is read where it is (within the call); anything else is converted and range-checked
-    if type(x) is np.ndarray and x.dtype == _I32 and x.flags.c_contiguous and x.ndim > 0:
+    # an aligned int32 array is read where it is (within the call); anything else is converted and range-checked
+    if type(x) is np.ndarray and x.dtype == _I32 and x.flags.c_contiguous and x.flags.aligned and x.ndim > 0:
         return x
     a = np.ascontiguousarray(np.asarray(x, dtype=np.int64))
     if a.size and (a.min() < -2**31 or a.max() >= 2**31):

@@ -214,3 +214,13 @@ def test_context_creation_without_gpu(lib):
     h = ctypes.c_void_p()
     assert lib.sa_create(0, ctypes.byref(h)) == 8       # SA_ERR_DEVICE
     assert not h.value
+
+
+def test_host_lengths_off_alignment_are_copied():
+    """The library reads the host arrays as int32: one that starts between words is copied, an aligned one is not."""
+    off = np.zeros(17, dtype=np.uint8)[1:].view(np.int32)
+    off[:] = [3, 1, 4, 1]
+    got = sa._host_i32(off)
+    assert not off.flags.aligned and got.flags.aligned and got.ctypes.data % 4 == 0 and got.tolist() == [3, 1, 4, 1]
+    own = np.array([3, 1], dtype=np.int32)
+    assert sa._host_i32(own) is own
