@@ -967,11 +967,19 @@ sa_status attn_launch(sa_ctx* ctx, const sa_layout* layout, int32_t layer, const
   if (n_parts > 0 && !noalloc) {
     const size_t need = (size_t)n_parts * rows_item * (sa::kHD + 1) * sizeof(float);
     if (need > ctx->part_cap) {
-      if (ctx->part) ctx->retired_dev.push_back(ctx->part);    // an enqueued merge may still read it
+      // at least doubled: part counts follow the lengths, and each growth is an
+      // allocation in the call whose outgrown buffer stays until sa_destroy
+      size_t cap = std::max(need, 2 * ctx->part_cap);
+      if (ctx->part) ctx->retired_dev.push_back(ctx->part);    // an enqueued launch may still use it
       ctx->part = nullptr;
       ctx->part_cap = 0;
-      SA_HIP(hipMalloc(&ctx->part, need));
-      ctx->part_cap = need;
+      if (cap > need && hipMalloc(&ctx->part, cap) != hipSuccess) {
+        (void)hipGetLastError();
+        ctx->part = nullptr;
+        cap = need;                                            // no room for twice as much: what the launch takes
+      }
+      if (ctx->part == nullptr) SA_HIP(hipMalloc(&ctx->part, cap));
+      ctx->part_cap = cap;
     }
   }
 

@@ -117,3 +117,25 @@ def test_missing_pages_of_a_split_decode_item_are_reported():
         sa.sa_segment_prefill_attn(ctx, L, 0, q, kp, vp, w.qlen, w.kv, ip, ix, w.scale, o)
         sa.sa_sync_check(ctx)
         compare(host_u16(o), ref, 2e-2, 2e-3)
+
+
+def test_split_buffer_grows_by_doubling():
+    """A context whose part counts creep up call by call (16, 24, ... 256 parts of 66 KB) allocates for
+    them at 16, 24, 40, 72 and 136 parts, not at each of the 31."""
+    L = sa.Layout(num_q_heads=8, num_kv_heads=8, head_dim=128, page_size=32, num_layers=1, num_slots=256)
+    pools = [torch.zeros((256, 8, 32, 128), dtype=torch.int16, device="cuda") for _ in range(2)]
+    q = torch.zeros((1, 8, 128), dtype=torch.int16, device="cuda")
+    o = torch.zeros_like(q)
+    ip = torch.tensor([0, 256], dtype=torch.int32, device="cuda")
+    ix = torch.arange(256, dtype=torch.int32, device="cuda")
+    parts, free = [], []
+    with sa.Context(0) as ctx:
+        for k in range(2, 33):
+            kv = [256 * k]
+            parts.append(sa.sa_attn_plan_stats(L, [1], kv)["parts"])
+            sa.sa_segment_prefill_attn(ctx, L, 0, q, pools[0], pools[1], [1], kv, ip, ix, 0.088, o)
+            torch.cuda.synchronize()
+            free.append(torch.cuda.mem_get_info(0)[0])
+        sa.sa_sync_check(ctx)
+    assert parts == [8 * k for k in range(2, 33)]
+    assert sum(a != b for a, b in zip(free, free[1:])) <= 6
