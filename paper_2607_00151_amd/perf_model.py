@@ -86,11 +86,24 @@ def predict_context(coef, works):
 
 
 def fit_shape_model(works, times):
-    """Least squares t = c + alpha_d sum L + alpha_p sum A + beta excess + gamma split.
-    Returns (c, alpha_d, alpha_p, beta, gamma)."""
+    """Least squares of the relative errors of t = c + alpha_d sum L + alpha_p sum A + beta
+    excess + gamma split, no coefficient negative: each is the time of some work, and few
+    launches with nearly collinear terms otherwise trade one against another (a prefill
+    launch of at most one workgroup per CU has an excess proportional to its work), which
+    fails on other batches.  Returns (c, alpha_d, alpha_p, beta, gamma)."""
     X = np.array([[1.0, w.decode_keys, w.prefill_pairs, w.excess_tiles, w.split] for w in works])
-    coef, *_ = np.linalg.lstsq(X, np.asarray(times, dtype=np.float64), rcond=None)
-    return tuple(float(x) for x in coef)
+    y = np.asarray(times, dtype=np.float64)
+    X, y = X / y[:, None], np.ones_like(y)
+    best = (np.inf, np.zeros(X.shape[1]))
+    for mask in range(1, 1 << X.shape[1]):               # every set of terms: the best fit without a negative one
+        cols = [i for i in range(X.shape[1]) if mask >> i & 1]
+        c, *_ = np.linalg.lstsq(X[:, cols], y, rcond=None)
+        r = float(np.sum((X[:, cols] @ c - y) ** 2))
+        if c.min() >= 0 and r < best[0]:
+            full = np.zeros(X.shape[1])
+            full[cols] = c
+            best = (r, full)
+    return tuple(float(x) for x in best[1])
 
 
 def predict_shape(coef, works):

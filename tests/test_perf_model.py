@@ -102,15 +102,3 @@ def test_shape_fit_recovers_known_coefficients():
     t = pm.predict_shape(coef, works)
     got = pm.fit_shape_model(works, t)
     assert np.allclose(got, coef, rtol=1e-6, atol=1e-12)
-
-
-def test_shape_fit_is_plain_least_squares():
-    """On times that no coefficients give exactly, the fit is the one with the smallest sum of squared
-    errors in ms: its residual is orthogonal to every term."""
-    L = _layout()
-    works = [pm.features(qs, kvs, L) for _, qs, kvs in pm.profiling_batches()]
-    t = pm.predict_shape((0.012, 3.0e-8, 2.5e-10, 4.0e-4, 0.009), works) * (1 + 0.1 * np.cos(np.arange(len(works))))
-    r = t - pm.predict_shape(pm.fit_shape_model(works, t), works)
-    X = np.array([[1.0, w.decode_keys, w.prefill_pairs, w.excess_tiles, w.split] for w in works])
-    cos = X.T @ r / (np.linalg.norm(X, axis=0) * np.linalg.norm(r))
-    assert np.abs(cos).max() < 1e-9
