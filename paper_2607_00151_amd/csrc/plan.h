@@ -397,10 +397,10 @@ inline void plan_attn_items(const sa_layout* layout, const std::vector<SeqDesc>&
   }
   // Split long items by key range where there are too few to fill the chip:
   // one of a few block counts, whichever the model below says ends first.
-  // Measured on MI355X, per 64-key tile of a prefill item: 1.15 us where its
-  // block has a CU to itself, 1.6 us where two share one (a pair is 1.4x one
-  // alone; its blocks start and end 9 us slower); writing, reading and merging
-  // the partials of 128 rows costs a launch 19 us per 512 parts.
+  // Measured on MI355X, per 64-key tile of a prefill item: 0.93 us where its block
+  // has a CU to itself (1.15 us where more items than CUs keep the whole chip at it),
+  // 1.6 us where two share one; writing and merging the partials of 128 rows costs a
+  // launch 14 us per 512 parts, and the merge 0.6 us per part of one item.
   //
   // A launch of at most num_cu blocks, or at most 2 num_cu, splits its items by
   // the smallest chunk that fits, each into equal parts (a chunk with a rest, 61,
@@ -426,13 +426,14 @@ inline void plan_attn_items(const sa_layout* layout, const std::vector<SeqDesc>&
     struct RowTile {
       int64_t tiles;
       bool decode;
+      int rows;                                    // query rows of a decode item
     };
     std::vector<RowTile> rows;                     // of one KV head: the others are alike
     int64_t longest = 1, streamed = 0;             // streamed: tiles read at least once
     for (size_t i = 0; i < work.size(); ++i) {
       const Work& w = work[i];
       if (w.it.kvh != 0) continue;
-      rows.push_back({w.tiles, w.decode});
+      rows.push_back({w.tiles, w.decode, w.decode ? seqs[w.it.seq].q_len * G : 0});
       longest = std::max(longest, w.tiles);
       if (i + 1 == work.size() || work[i + 1].it.seq != w.it.seq || work[i + 1].it.kvh != 0)
         streamed += w.tiles * Hkv;                 // the sequence's last row tile sees the most keys
@@ -457,7 +458,56 @@ inline void plan_attn_items(const sa_layout* layout, const std::vector<SeqDesc>&
       }
       return lo;
     };
-    auto smallest_chunk = [&](int64_t slots) { return smallest_chunk_from(1, slots, INT64_MAX); };
+    // The block of an item's last part merges them all, so that is serial in their
+    // number: 0.6 us a part of a prefill item, 0.0125 us a part and row of a decode
+    // item, against about 0.9 and 0.6 us a tile.  Alone, an item of t tiles ends soonest
+    // in parts of sqrt(t / 1.5) or sqrt(rows t / 48) tiles; the optimum is flat, and
+    // among others a little finer is better, so no launch is split finer than its
+    // slowest item's sqrt(t / 2) or sqrt(rows t / 64).  Measured, us, of the most parts
+    // that fit the slots, of the rule's and of the best count -- prefill: 4 query tokens
+    // x 16 heads of one KV head over 30000 keys 82.7 (118 parts), 39.8 (32), 39.7 (24);
+    // 8 tokens over 120000 178 (255), 75.1 (61), 74.4 (47); 32 tokens x 4 heads of two KV
+    // heads over 32800 80.7 (103), 44.9 (33), 43.8 (26); decode: 4 tokens x 8 heads of one
+    // KV head over 100000 67.1 (128), 49.6 (56), 49.6; one token 25.7 (128), 24.8 (112),
+    // 24.8; 5 tokens x 4 heads of two KV heads over 16000 29.0 (63), 23.2 (28), 22.3 (21).
+    int64_t finest = 1;
+    for (const RowTile& w : rows) {
+      const double c = w.decode ? std::sqrt(w.rows * w.tiles / 64.0) * (any_pre ? 0.75 : 1.0) : std::sqrt(w.tiles / 2.0);
+      finest = std::max<int64_t>(finest, std::llround(c));
+    }
+    finest = std::min(finest, longest);
+    auto smallest_chunk = [&](int64_t slots) { return smallest_chunk_from(finest, slots, INT64_MAX); };
+    // the blocks of chunk c: their lengths in tiles of a prefill item's time, longest first
+    struct Run {
+      int64_t tiles, blocks;
+    };
+    std::vector<Run> runs;
+    auto lengths = [&](int64_t c, auto&& each) {
+      runs.clear();
+      for (const RowTile& w : rows) {
+        const int64_t k = parts_of(w.tiles, w.decode, c);
+        int64_t t = (w.tiles + k - 1) / k;
+        if (w.decode && any_pre) t -= t / 4;
+        runs.push_back({t, k * Hkv});
+        each(w, k);
+      }
+      std::sort(runs.begin(), runs.end(), [](const Run& x, const Run& y) { return x.tiles > y.tiles; });
+    };
+    // the most loaded CU of runs' n blocks, up to two a CU, at these costs of a tile alone
+    // and of a tile of each of two: the longest n - num_cu each with one of the shortest
+    auto busiest = [&](int64_t n, int64_t alone, int64_t both) {
+      int64_t busy = 0;
+      size_t i = 0, j = runs.size() - 1;
+      int64_t left_i = runs[0].blocks, left_j = runs[j].blocks, pairs = n - num_cu;
+      while (pairs > 0) {
+        busy = std::max(busy, both * runs[j].tiles + alone * (runs[i].tiles - runs[j].tiles));
+        const int64_t step = i == j ? pairs : std::min(pairs, std::min(left_i, left_j));
+        pairs -= step;
+        if ((left_i -= step) <= 0 && i < j) left_i = runs[++i].blocks;
+        if ((left_j -= step) <= 0 && j > i) left_j = runs[--j].blocks;
+      }
+      return std::max(busy, alone * runs[i].tiles);
+    };
     int64_t chunk = longest;                       // whole items
     if (n_work <= num_cu && !any_pre) {
       // decode requests alone: a part for every CU, or two where that would leave
@@ -466,18 +516,22 @@ inline void plan_attn_items(const sa_layout* layout, const std::vector<SeqDesc>&
       chunk = smallest_chunk(num_cu);
       if (total_tiles * 7 < 6 * chunk * num_cu) chunk = smallest_chunk(2 * num_cu);
     } else if (n_work <= num_cu) {
-      const int64_t c1 = smallest_chunk(num_cu), c2 = smallest_chunk(2 * num_cu);
-      int64_t p1, p2;
-      const int64_t n1 = count(c1, p1), n2 = count(c2, p2);
-      auto cost = [&](int64_t c, int64_t n, int64_t parts) {
-        int64_t most = 0;                          // tiles of the longest part
-        for (const Work& w : work) {
-          const int64_t k = parts_of(w.tiles, w.decode, c), t = (w.tiles + k - 1) / k;
-          most = std::max(most, w.decode ? t - t / 4 : t);
-        }
-        return (n <= num_cu ? 115 * most : 160 * most + 900) + 1900 * parts / 512;
+      // one block per CU or two, whichever ends first by its pairs and the merge of its
+      // most split item, in units of 10 ns: a tile 93 alone on its CU, 160 for a tile of
+      // each of two blocks, 1400 for the partials of 512 parts (over 136 prefill and mixed
+      // launches of 1 to 240 items measured both ways the choice is on average 0.4% slower
+      // than the better one; by the longest part instead of the pairs 1.2%)
+      auto cost = [&](int64_t c) {
+        int64_t n = 0, parts = 0, merged = 0;      // merged: parts of the most split prefill item
+        lengths(c, [&](const RowTile& w, int64_t k) {
+          n += k * Hkv;
+          if (k > 1) parts += k * Hkv;
+          if (!w.decode) merged = std::max(merged, k);
+        });
+        return busiest(n, 93, 160) + 1400 * parts / 512 + 60 * merged;
       };
-      chunk = cost(c2, n2, p2) < cost(c1, n1, p1) ? c2 : c1;
+      const int64_t c1 = smallest_chunk(num_cu), c2 = smallest_chunk(2 * num_cu);
+      chunk = cost(c2) < cost(c1) ? c2 : c1;
     } else {
       // Whole items, the smallest chunk that fits two blocks per CU (one long
       // context among many short ones: its parts fill the slots the others leave),
@@ -497,37 +551,17 @@ inline void plan_attn_items(const sa_layout* layout, const std::vector<SeqDesc>&
       // 1895, 605, 590, 605.
       const int64_t alone = any_pre ? 115 : 80, both = any_pre ? 160 : 210, slots = 2 * num_cu;
       const int64_t stream = any_pre ? streamed * 61 / 100 : streamed * 546 / 1000;
-      struct Run {
-        int64_t tiles, blocks;
-      };
-      std::vector<Run> runs;                       // blocks of one length, longest first
       auto cost = [&](int64_t c) {
-        runs.clear();
         int64_t n = 0, sum = 0, parts = 0, prefill_parts = 0;
-        for (const RowTile& w : rows) {
-          const int64_t k = parts_of(w.tiles, w.decode, c);
-          int64_t t = (w.tiles + k - 1) / k;
-          if (w.decode && any_pre) t -= t / 4;
-          runs.push_back({t, k * Hkv});
+        lengths(c, [&](const RowTile& w, int64_t k) {
           n += k * Hkv;
-          sum += t * k * Hkv;
+          sum += runs.back().tiles * k * Hkv;
           if (k > 1) parts += k * Hkv;
           if (k > 1 && !w.decode) prefill_parts += k * Hkv;
-        }
-        std::sort(runs.begin(), runs.end(), [](const Run& x, const Run& y) { return x.tiles > y.tiles; });
+        });
         int64_t busy = 0;                          // the most loaded CU
         if (n <= slots) {
-          // the longest n - num_cu blocks each with one of the shortest, the others alone
-          size_t i = 0, j = runs.size() - 1;
-          int64_t left_i = runs[0].blocks, left_j = runs[j].blocks, pairs = n - num_cu;
-          while (pairs > 0) {
-            busy = std::max(busy, both * runs[j].tiles + alone * (runs[i].tiles - runs[j].tiles));
-            const int64_t step = i == j ? pairs : std::min(pairs, std::min(left_i, left_j));
-            pairs -= step;
-            if ((left_i -= step) <= 0 && i < j) left_i = runs[++i].blocks;
-            if ((left_j -= step) <= 0 && j > i) left_j = runs[--j].blocks;
-          }
-          busy = std::max(busy, alone * runs[i].tiles);
+          busy = busiest(n, alone, both);
         } else {
           const int64_t t = (sum + n - 1) / n + (any_pre ? 5 : 0);   // each block's own start and end
           const int64_t rest = n % slots;
@@ -541,6 +575,7 @@ inline void plan_attn_items(const sa_layout* layout, const std::vector<SeqDesc>&
       const int64_t mean = (total_tiles + n_work - 1) / n_work;
       int64_t best = cost(longest);
       auto consider = [&](int64_t c) {
+        c = std::max(c, finest);
         const int64_t t = c < longest ? cost(c) : best;
         if (t < best) {
           best = t;

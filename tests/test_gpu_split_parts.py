@@ -33,7 +33,8 @@ CASES = {
     "unseen_parts": (8, 2, 16, [700, 10], [100, 300]),
     "ragged_decode": (8, 1, 16, [100, 20000, 3000, 0, 64], [1, 1, 1, 1, 1]),
     "mixed": (8, 1, 16, [4000, 4000, 900], [1, 200, 1]),
-    "part_limit_32_rows": (32, 1, 32, [40000], [1]),
+    "part_limit_8_rows": (8, 1, 32, [190000], [1]),
+    "part_limit_32_rows": (32, 1, 32, [720000], [1]),
     # 320 and 448 items, one long context among short ones: more than CUs, not two per CU
     "long_among_short": (64, 64, 16, [6000, 300, 300, 300, 300], [1, 1, 1, 1, 1]),
     "long_among_short_mixed": (128, 64, 16, [6000, 300, 300, 300, 300], [40, 100, 70, 1, 1]),
@@ -71,7 +72,7 @@ def test_split_items(name, entry):
     st = sa.sa_attn_plan_stats(layout_of(w), w.qlen, w.kv)
     print(f"{name} {entry}: {st}", flush=True)
     assert st["parts"] > 0 and st["items"] < 2 ** 14
-    if name.startswith("part_limit"):          # as many as the merge has LDS for
+    if name.startswith("part_limit_"):         # as many as the merge has LDS for
         assert st["parts"] == 128
     with sa.Context(0) as ctx:
         check(w, launches(ctx, w, getattr(sa, entry)))
