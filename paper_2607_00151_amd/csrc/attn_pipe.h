@@ -110,9 +110,11 @@ __device__ __forceinline__ bool table_check_finish(const AttnArgs& a, TableCheck
 // With kRead every block takes the segment's keys (positions kv_len - q_len
 // on) from the token-major k_new / v_new and never from their pages, so no
 // block depends on another block's writes.  The first key-range part of each
-// row tile (kv_begin == 0) stores to the pages the rows of the tokens whose
-// first query row lies in its tile: the row tiles partition the rows, so every
-// token's row is written exactly once.  A row whose page is missing or lies
+// row tile (kv_begin == 0; of a decode item's, those with keys of the segment)
+// stores to the pages the rows of the tokens whose first query row lies in its
+// tile: the row tiles partition the rows, so every token's row is written, and
+// by one block (or, where a decode item's segment crosses a part's edge, with
+// the same bytes by both).  A row whose page is missing or lies
 // outside the pool is not written and raises error flag 2, as the append
 // kernel does.  Four chunks per thread are loaded before any is stored, so the
 // block waits for one round trip per 1024 chunks (64 tokens).
@@ -1418,10 +1420,13 @@ __device__ __attribute__((always_inline)) inline void decode_group(const AttnArg
 
 // One group of four waves per block, two blocks per CU.
 // kRead: the launch also writes the segment's new K/V rows (write_own_rows)
-// and reads the segment's keys from them, not from their pages.  A whole decode
-// item reads its keys through the pages: it is the only reader of its rows, so
-// it writes them itself first and reads them back after a barrier; the parts of
-// a split one take the general path, which reads them from k_new / v_new.
+// and reads the segment's keys from them, not from their pages.  A decode item
+// reads its keys through the pages, whole or split: a part with keys of the
+// segment writes all of the item's rows itself first and reads them back after a
+// barrier, so it depends on no other block (one part has them all unless the
+// segment's up to 32 keys cross a part's edge; then both write the same bytes).
+// One 16570-key request, 8 heads over two KV heads, append included: 52.3 us with
+// its parts on the general path, 13.3 on this one.
 // kExact: the softmax scale is applied in fp32 to each score instead of to
 // the query rows in bf16 (one fma per score; no rounding of c q).
 template <int P, bool kPoolRsrc, bool kRead, bool kExact = false>
@@ -1443,9 +1448,9 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_kernel(AttnArgs a) {
     const PipeLds L{(lds_u8*)k_lds0, (lds_u8*)k_lds1, (lds_u8*)v_lds0, (lds_u8*)v_lds1,
                     nullptr, nullptr, nullptr, nullptr, nullptr};
     // the parts of a split item all take one path, since they share its partials' layout
-    const bool decode = it.q_len * a.G <= kDecRows && (!kRead || it.part < 0);
+    const bool decode = it.q_len * a.G <= kDecRows;
     if constexpr (kRead) {
-      if (it.kv_begin == 0) {
+      if (decode ? it.kv_end > it.kv_len - it.q_len : it.kv_begin == 0) {
         write_own_rows<P>(a, it);
         if (decode) __syncthreads();                         // its own rows, read back below
       }

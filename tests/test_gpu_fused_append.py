@@ -9,9 +9,8 @@ built on the transformed prefix).  For every case:
   two, canary everywhere nothing is written);
 * every output row and LSE matches the fp64 oracle (sampled rows at the full
   c2 size);
-* where both forms take the same kernel steps -- every prefix a multiple of 4
-  keys and no request of at most 32 query rows -- output and LSE equal
-  those of the two-launch form (sa_set_fused_append(ctx, 0): append kernel,
+* where both forms take the same kernel steps -- the prefix of every request of more
+  than 32 query rows a multiple of 4 keys -- output and LSE equal those of the two-launch form (sa_set_fused_append(ctx, 0): append kernel,
   then attention) bit for bit; elsewhere both meet the oracle's bar.
 """
 import numpy as np
@@ -73,13 +72,11 @@ def check_pools(w, kp, vp, before, layer=1):
 
 
 def same_steps(w):
-    """Both forms run the same kernel steps: prefixes are multiples of 4 keys (no group
-    of four keys mixes prefix and segment rows) and no request has at most 32 query rows
-    (the fused form sends the later key-range parts of such a request, when the plan
-    splits it, through the general path)."""
+    """Both forms run the same kernel steps: requests of at most 32 query rows read all their
+    keys from the pages in either form, and the other prefixes are multiples of 4 keys (no
+    group of four keys mixes prefix and segment rows)."""
     G = w.num_q_heads // w.num_kv_heads
-    decode = [b for b in range(w.batch) if 0 < int(w.qlen[b]) * G <= 32]
-    return all(int(p) % 4 == 0 for p in w.pre) and not decode
+    return all(int(p) % 4 == 0 for p, q in zip(w.pre, w.qlen) if int(q) * G > 32)
 
 
 def check_case(ctx, w, folded=False):
@@ -134,6 +131,18 @@ def test_fused_split_and_decode(ctx):
     """Key-range split items (few long requests), some of at most 32 rows that read the
     rows they wrote, and later parts that hold segment keys."""
     check_case(ctx, build("split", 21, 8, 1, 128, 16, [5000, 3000, 70, 0], [1, 1, 3, 1]))
+
+
+@pytest.mark.parametrize("pre", [2000, 2017, 2040, 2047, 2048])
+@pytest.mark.parametrize("heads,q", [((8, 1), 1), ((8, 2), 8), ((1, 1), 32), ((17, 1), 1)])
+def test_fused_split_decode_parts(ctx, heads, q, pre):
+    """Split requests of 4 to 32 rows beside short ones, their segment before, across and
+    after a tile's edge: the parts with segment keys write the rows and read them back, the
+    others read the prefix, and the result is the two-launch form's bit for bit."""
+    w = build(f"dec_{pre}_{q}", 9400 + pre + q, *heads, 128, 16, [pre, 30, 9 * pre], [q, 1, q])
+    st = sa.sa_attn_plan_stats(layout_of(w), w.qlen, w.kv)
+    assert st["parts"] > 2 * heads[1] and same_steps(w)
+    check_case(ctx, w)
 
 
 @pytest.mark.parametrize("k", range(3))
