@@ -86,14 +86,17 @@ def predict_context(coef, works):
 
 
 def fit_shape_model(works, times):
-    """Least squares of the relative errors of t = c + alpha_d sum L + alpha_p sum A + beta
-    excess + gamma split, no coefficient negative: each is the time of some work, and few
-    launches with nearly collinear terms otherwise trade one against another (a prefill
-    launch of at most one workgroup per CU has an excess proportional to its work), which
-    fails on other batches.  Returns (c, alpha_d, alpha_p, beta, gamma)."""
+    """Least squares t = c + alpha_d sum L + alpha_p sum A + beta excess + gamma split, no
+    coefficient negative: each is the time of some work, and few launches with nearly
+    collinear terms otherwise trade one against another (a prefill launch of at most one
+    workgroup per CU has an excess proportional to its work), which fails on other batches.
+    The errors are in ms, not relative to the launch: what the model is asked for is the
+    time of batches about as long as the longest profiled, and with relative errors those
+    came out 8-10% short, with these 3-4% (five sweeps; fitted on the single-kind launches
+    alone, the mixed ones are off by 7.3% on average, 7.9% with relative errors).
+    Returns (c, alpha_d, alpha_p, beta, gamma)."""
     X = np.array([[1.0, w.decode_keys, w.prefill_pairs, w.excess_tiles, w.split] for w in works])
     y = np.asarray(times, dtype=np.float64)
-    X, y = X / y[:, None], np.ones_like(y)
     best = (np.inf, np.zeros(X.shape[1]))
     for mask in range(1, 1 << X.shape[1]):               # every set of terms: the best fit without a negative one
         cols = [i for i in range(X.shape[1]) if mask >> i & 1]

@@ -102,3 +102,17 @@ def test_shape_fit_recovers_known_coefficients():
     t = pm.predict_shape(coef, works)
     got = pm.fit_shape_model(works, t)
     assert np.allclose(got, coef, rtol=1e-6, atol=1e-12)
+
+
+def test_shape_fit_is_the_best_one_without_negative_terms():
+    """On times that no coefficients give exactly, the fit minimises the squared errors in ms over
+    non-negative coefficients: the gradient is zero along the terms it uses and points up along the others."""
+    L = _layout()
+    works = [pm.features(qs, kvs, L) for _, qs, kvs in pm.profiling_batches()]
+    X = np.array([[1.0, w.decode_keys, w.prefill_pairs, w.excess_tiles, w.split] for w in works])
+    for coef in ((0.012, 3.0e-8, 2.5e-10, 4.0e-4, 0.009), (0.012, 3.0e-8, 2.5e-10, 0.0, -0.02)):
+        t = pm.predict_shape(coef, works) * (1 + 0.1 * np.cos(np.arange(len(works))))
+        got = np.array(pm.fit_shape_model(works, t))
+        r = t - pm.predict_shape(got, works)
+        cos = X.T @ r / (np.linalg.norm(X, axis=0) * np.linalg.norm(r))
+        assert got.min() >= 0 and np.abs(cos[got > 0]).max() < 1e-9 and cos.max() < 1e-9
