@@ -421,8 +421,8 @@ def config_mode(args):
         "config": {"workload": f"{w.name}: batch {w.batch}, Hq {Hq} / Hkv {Hkv} / d 128, page {P}, "
                                f"prefix {int(w.pre.min())}..{int(w.pre.max())}, segment {int(w.qlen.min())}.."
                                f"{int(w.qlen.max())}", "segment_tokens": T, "cached_keys": int(w.kv.sum())},
-        "attn": {"ms": attn_ms, "timing": "kernel events (the attention kernel; a split launch's merge not "
-                                          "included)", "call_ms": attn_call_ms,
+        "attn": {"ms": attn_ms, "timing": "kernel events (the attention kernel, which merges the parts of a "
+                                          "split launch)", "call_ms": attn_call_ms,
                  "xcd_speeds": None if xcd_speed is None else [round(float(x), 4) for x in xcd_speed],
                  "gflop": flops / 1e9, "tflops": tflops, "frac_of_bf16_peak": tflops / PEAK_BF16_TFLOPS},
         first_name: {"ms": first_ms, "timing": "kernel events" if one_page_kernel else "call events",

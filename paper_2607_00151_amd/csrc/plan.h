@@ -731,8 +731,12 @@ inline void plan_attn_items(const sa_layout* layout, const std::vector<SeqDesc>&
   // In a mixed launch the prefill items run at raised priority throughout: a
   // decode item's waves mostly wait for HBM, and being the older blocks of their
   // CUs they would otherwise win the SIMDs' issue from the prefill item that
-  // bounds the launch (4 segments of 2048 over 16K with 64 decode rows: 2273
-  // against 2295 us).
+  // bounds the launch.  With and without, us, in turn on one GPU (runs of one side
+  // within 0.5%): 64 decode rows and 4 segments of 2048 over 16K 2156, 2199; 16 rows
+  // of 8-32K and 4096 over 32K 2142, 2155; 32 of 4K and 512 over 4K 128, 140; 64 of
+  // 1-4K and 256 over 8K 191, 199.  The decode rows' blocks end later inside the
+  // launch (467 against 450, 605 against 540, 107 against 100, 121 alike), but their
+  // outputs are ready, as all of the launch's, when it ends.
   if (mixed)
     for (AttnItem& x : items)
       if (x.kv_end > x.kv_begin && (int64_t)x.q_len * G > kDecodeRows) x.boost = (int32_t)item_tiles(x);
