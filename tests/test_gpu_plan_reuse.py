@@ -7,10 +7,11 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_2607_00151_amd as sa
 from workloads.configs import build
 
-from harness import build_cache, build_source_cache, dev_u16, layout_of
+from harness import build_cache, build_source_cache, compare, dev_u16, host_u16, layout_of
 
 pytestmark = pytest.mark.gpu
 
@@ -111,6 +112,21 @@ def test_arrival_counters_left_off_are_reported_and_cleared(entry):
         o, lse = attend(fn, ctx, w, cache)
         assert torch.equal(o, want[0]) and torch.equal(lse, want[1])
         sa.sa_sync_check(ctx)
+
+
+@pytest.mark.parametrize("entry", ["sa_segment_prefill_attn", "sa_segment_prefill_attn_noalloc"])
+@pytest.mark.parametrize("batch", [200, 285, 291, 299, 583, 595, 1165, 1185])
+def test_plans_of_one_and_several_copies(batch, entry):
+    """One item a request (56 bytes of plan): plans around 16, 32 and 64 KB, which go to the device in
+    one copy, in pieces or in one copy again; every row against the oracle."""
+    r = np.random.default_rng(batch)
+    w = build("pieces", 320 + batch, 2, 1, 128, 16, [int(x) for x in r.integers(0, 40, batch)], [1] * batch)
+    with sa.Context(0) as ctx:
+        o, lse = attend(getattr(sa, entry), ctx, w, build_cache(w))
+        sa.sa_sync_check(ctx)
+    ref, ref_lse, _ = oracle.attention_all(w.q, w.k, w.v, w.q_indptr, w.kv_indptr, 2, 1, w.scale)
+    compare(host_u16(o), ref, 2e-2, 2e-3)
+    assert np.abs(lse.cpu().numpy() - ref_lse).max() <= 1e-3
 
 
 @pytest.mark.parametrize("mode", ["copy", "alias"])
