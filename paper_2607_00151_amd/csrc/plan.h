@@ -690,6 +690,21 @@ inline void plan_attn_items(const sa_layout* layout, const std::vector<SeqDesc>&
   if (mx > 0 && (double)(mx - mn) <= 0.1 * (double)mx) {
     std::vector<std::vector<AttnItem>> queue(kNumXcd);
     for (const Work& w : work) queue[w.xcd].push_back(w.it);
+    // No XCD gets more blocks than its share of the slots of a launch that fits one
+    // block per CU, or two: its CUs would take turns while others idle (15 decode
+    // requests of 14-51K keys, 32/4 heads: 256 parts, 33 of them on some XCDs, 238 us,
+    // with 32 on each 177).  The shortest items move; with them goes at most a tile read
+    // twice.
+    const size_t n_blocks = work.size(), rounds = (n_blocks + num_cu - 1) / num_cu;
+    if (rounds <= 2)
+      for (auto& q : queue)
+        while (q.size() > rounds * xcd_round) {
+          auto least = std::min_element(queue.begin(), queue.end(),
+                                        [](const auto& x, const auto& y) { return x.size() < y.size(); });
+          if (least->size() >= rounds * xcd_round) break;
+          least->push_back(q.back());
+          q.pop_back();
+        }
     if (xcd != nullptr && xcd->weighted && !mixed) {
       bool same = xcd->in.size() == queue.size();
       for (size_t x = 0; same && x < queue.size(); ++x)

@@ -218,6 +218,15 @@ static void check_part_cap(std::mt19937_64& r, int case_id) {
           g.nsplit, decode ? "decode" : "prefill");
     g_most_parts[decode] = std::max(g_most_parts[decode], g.nsplit);
   }
+  // block i runs on XCD i % 8: a launch that fits one block per CU, or two, does so on every XCD
+  int64_t blocks = 0, on[sa::kNumXcd] = {0};
+  for (size_t i = 0; i < free_plan.items.size(); ++i)
+    if (free_plan.items[i].kv_end > free_plan.items[i].kv_begin) ++blocks, ++on[i % sa::kNumXcd];
+  const int64_t rounds = (blocks + shape.num_cu - 1) / shape.num_cu;
+  if (rounds <= 2)
+    for (int x = 0; x < sa::kNumXcd; ++x)
+      CHECK(on[x] <= rounds * shape.num_cu / sa::kNumXcd, "case %d: %lld blocks, %lld of them on XCD %d", case_id,
+            (long long)blocks, (long long)on[x], x);
   for (int64_t cap : {(int64_t)8192, (int64_t)476, (int64_t)(1 + r() % 300)}) {
     shape.max_parts = cap;
     sa::plan_attn_items(&L, seqs, shape, nullptr, capped);
